@@ -3,37 +3,45 @@
 // Paper: section 3, eq. 3 (the weight), section 18 (kernel work across
 // shapes and batch sizes is the stated next step).  For a batch of B
 // activation rows the product is a dense contraction, so it runs on
-// v_mfma_f32_16x16x32_f16: A = 16 weight rows, B = 16 batch rows, C = the
-// 16 x 16 block of Y^T.
+// v_mfma_f32_16x16x32_f16: A = 16 batch rows, B = 16 weight rows, C = the
+// 16 x 16 block of Y.
 //
-// k order.  MFMA sums over k in any order, so the 32 k of a step are chosen
-// to make both operands cheap.  Groups are taken four at a time (a quad);
-// lane block q (lanes 16q .. 16q+15) works on group 4Q + q in every step of
-// quad Q, and step u (0..15) takes inputs 8u .. 8u+7 of each block's group.
-// The B operand is then one aligned 16-byte chunk of X per lane, and the
-// code bytes and trit phase of a window (its first input is trit 8u % 5 of
-// byte 8u / 5) are fixed per step, known at compile time.
+// k order.  MFMA sums over k in any order, so a group's 128 inputs are laid
+// on the four lane blocks (lanes 16q .. 16q+15) by whole code bytes: block
+// q < 3 takes code bytes 8q .. 8q+7 (40 trits, inputs 40q .. 40q+39), block 3
+// the two tail bytes (inputs 120 .. 127); its other inputs read as zeros.
+// The 40 trits are five windows of 8, one per MFMA, so every lane decodes
+// its 8 bytes with the same code, and the X operand of window u is the
+// aligned 16-byte chunk of X at input 40q + 8u.  (Five k-steps for 128
+// inputs, four would be the minimum; in exchange a step holds one group.)
 //
-// Decode.  The GEMV's table (fp16 +-1/0 patterns (t0,t1), (t2,t3), (t4,0)
-// per code, 16 copies, static LDS) is read once per code byte, with one
-// 16-byte read (a byte shared by two windows is kept in registers); a window's four dwords
-// are table dwords or two of them joined by v_alignbit / v_lshl_or.  A
-// weight is pattern * s0 + offset in one v_pk_fma_f16 (exact without
-// offsets); on two-plane groups the plane-1 pattern * s1 is added with one
-// more fma and the record's offset is folded into the plane-0 term, so a
-// weight takes at most three fp16 roundings (well inside the accuracy
-// bound).
+// Decode.  A table in LDS maps a code to the high bytes of its five fp16
+// trits (+1 = 0x3C00, 0, -1 = 0xBC00) in 8 bytes; a pair of trits is one
+// v_perm of two entries.  The weights of the operand are the bare trits: as
+// every MFMA of an accumulator belongs to one group, s0 multiplies the
+// group's fp32 sums, four per 16 x 16 block and lane, instead of every
+// weight, and no weight is rounded to fp16.  A lane's four sums belong to
+// the weight row it decoded, so its scale, offset and record are its own.
+// Offsets multiply the group's sum of x, one more tile with ones as weights.
 //
-// Work split.  A workgroup of 8 waves owns 16 RT consecutive rows.  Its
-// waves split K by quads, and each wave covers all RT row tiles and all
-// batch columns, so a CU reads its slice of X once and decodes every weight
-// once.  Plane-0 codes go straight to registers, all loaded up front; X
-// comes in bursts of a whole line per lane, one burst ahead of use.  The
-// workgroup's plane-1 records are staged in LDS with one slot per (row,
-// group).  The waves' partial sums are added in a fixed order through LDS
-// (bit-reproducible).  Shapes past the register and LDS limits (more than
-// four quads per wave) use the simple per-group kernel at the end of this
-// file.
+// Plane 1.  The workgroup's records are staged in LDS by (group, row % 16):
+// a group's records are decoded as one more row tile whose row n holds a
+// record of one of the weight rows n, n + 16, ..., and s1 times its sums is
+// added to the totals of that row, which are in the same lane.  Rows that
+// share n and both have a record take one more pass each (10 % two-plane
+// groups and three row tiles: 1.4 passes a group, where decoding plane 1
+// along with every row tile under a per-lane branch cost as much as three).
+//
+// Work split.  A workgroup of 8 waves owns 16 RT consecutive rows and the
+// waves take the groups in turn, each wave all row tiles and all batch
+// columns of its group, so every weight is decoded once and a CU reads X
+// once.  A wave streams the codes of its groups through registers, kRing
+// groups ahead, without waiting for the other waves; tails, scales and
+// records are staged in LDS, for chunks of groups where a row is too long.
+// The waves' partial sums are added in a fixed order through LDS
+// (bit-reproducible).
+
+#include <unordered_map>
 
 #include "tq_internal.h"
 
@@ -41,124 +49,123 @@ namespace tq {
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 
 constexpr int kLdsLimit = 160 * 1024;
-constexpr int kQWaves = 8;                       // waves per workgroup (K split)
-constexpr int kQThreads = 64 * kQWaves;
-constexpr int kQRep = 16;                        // table copies (lane & 15)
-constexpr int kQLutBytes = 256 * kQRep * 16;     // 64 KiB
-constexpr int kQMaxPairs = 2048;                 // record slots (rows x groups) per workgroup
-constexpr int kQMaxUnits = 4;                    // row tiles x quads per wave
-constexpr int kWindows = 16;                     // 8-input k blocks per group
+constexpr int kWaves = 8;                            // two per SIMD
+constexpr int kThreads = 64 * kWaves;
+constexpr int kRing = 2;                             // groups of a wave whose codes are in registers or in flight
+constexpr int kLutCopies = 32;                       // 8-byte entries: 32 lanes cover the 64 banks once
+constexpr int kLutBytes = 256 * kLutCopies * 8;      // 64 KiB
+constexpr int kMaxPairs = 1536;                      // (row, group) pairs staged at a time
+constexpr int kMaxRanges = 640;                      // workgroups with record ranges in the kernel arguments
+constexpr uint32_t kOnes = 0x3C003C00u;
+
+// Arguments behind the leading ones, which arrive in SGPRs.
+struct TileArgs {
+  const uint16_t* offset0;
+  const uint8_t* codes1;
+  const uint16_t* gidx1;
+  const uint16_t* offset1;
+  const uint16_t* scale1;
+  void* Y;
+  // With ranges from the host row pointers: the first record of every
+  // workgroup, then nnz1, so record loads need no dependent load.
+  int32_t rec_begin[kMaxRanges + 1];
+};
+
+// Dynamic LDS of a workgroup of R = 16 RT rows, NW waves and a chunk of C
+// groups (byte offsets): per wave 16 rows of a group of X, with 16 bytes
+// between rows so that one 16-byte read's 16 rows cover the banks; 64 zero
+// bytes; the 32-byte record slots [group][pass][16] (code bytes 0..23, tail,
+// row tile, s1 | mu << 16); a byte per (group, row % 16) with its number of
+// records; per row and group the word tail | s0 << 16 and the offset, with an
+// odd row stride so that 16 rows spread over the banks.  After the main loop
+// the partial sums [waves][RT][CT][64 lanes] x 16 B overlay it.
+constexpr int kXRow = 2 * kGroup + 16;
+__host__ __device__ constexpr int tile_stride(int C) { return C | 1; }
+__host__ __device__ constexpr int tile_zero_off(int NW) { return NW * 16 * kXRow; }
+__host__ __device__ constexpr int tile_slot_off(int NW) { return tile_zero_off(NW) + 64; }
+__host__ __device__ constexpr int tile_count_off(int NW, int R, int C) { return tile_slot_off(NW) + 32 * R * C; }
+__host__ __device__ constexpr int tile_word_off(int NW, int R, int C) { return tile_count_off(NW, R, C) + 16 * C; }
+__host__ __device__ constexpr int tile_offset_off(int NW, int R, int C) {
+  return tile_word_off(NW, R, C) + 4 * R * tile_stride(C);
+}
+__host__ __device__ constexpr int tile_lds(int NW, int R, int C, bool off) {
+  return tile_offset_off(NW, R, C) + (off ? 4 * R * tile_stride(C) : 0);
+}
+__host__ __device__ constexpr int tile_red_bytes(int NW, int RT, int CT) { return NW * RT * CT * 64 * 16; }
+static_assert(kLutBytes + tile_lds(8, 16, 96, true) <= kLdsLimit && kLutBytes + tile_lds(8, 32, 48, true) <= kLdsLimit &&
+                  kLutBytes + tile_lds(8, 48, 32, true) <= kLdsLimit && kLutBytes + tile_lds(8, 64, 24, true) <= kLdsLimit,
+              "a full chunk fits");
 
 __device__ inline float h2f(uint32_t b) { return (float)__builtin_bit_cast(_Float16, (uint16_t)b); }
 __device__ inline uint32_t f2h(float a) { return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)a); }
 
-struct __attribute__((aligned(16))) U3 {
-  uint32_t x, y, z;
-};
-
-constexpr int kQMaxRanges = 640;   // workgroups with record ranges in the kernel arguments
-
-struct QArgs {
-  MatDev m;
-  const uint16_t* X;
-  void* Y;
-  int B;
-  int out_f32;
-  // With kHost: the first record of every workgroup, then nnz1 (from the
-  // host row pointers), so record loads need no dependent load.
-  int32_t rec_begin[kQMaxRanges + 1];
-};
-
-// LDS: the table (the kernel's only static array, so it sits at LDS address
-// 0 and the byte-to-address v_perm is the whole address; in the dynamic
-// block it cost an add per read), then the dynamic part: row pointers [R + 1], record flags
-// [R * G], record slots [R * G] x 32 B (byte offsets below); after the main
-// loop the partial sums [waves][RT][CT][64 lanes] x 16 B overlay it.
-__host__ __device__ constexpr int q_flag_off(int R) { return 4 * (R + 1); }
-__host__ __device__ constexpr int q_rec_off(int R, int G) { return (q_flag_off(R) + R * G + 15) & ~15; }
-__host__ __device__ constexpr int q_stage_bytes(int R, int G) { return q_rec_off(R, G) + 32 * R * G; }
-__host__ __device__ constexpr int q_red_bytes(int RT, int CT) { return kQWaves * RT * CT * 64 * 16; }
-
-__device__ inline uint32_t q_pattern(int t) { return t > 0 ? 0x3C00u : (t < 0 ? 0xBC00u : 0u); }
-
-// Table entry of code c: fp16 patterns of (t0, t1), (t2, t3), (t4, 0);
-// codes 243..255 read as zeros.
-__device__ inline uint4 q_entry(int c) {
+// Table entry of code c: the high bytes of the fp16 patterns of t0..t3 and,
+// in the second dword, t4; codes 243..255 read as zeros.
+__device__ inline u2v table_entry(int c) {
   uint32_t t[5];
   uint32_t d = (uint32_t)c;
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
     const uint32_t qd = (d * 171u) >> 9;   // d / 3 for d < 256
-    t[i] = c < 243 ? q_pattern((int)(d - 3u * qd) - 1) : 0u;
+    const uint32_t u = d - 3u * qd;
+    t[i] = c >= 243 || u == 1u ? 0u : (u == 2u ? 0x3Cu : 0xBCu);
     d = qd;
   }
-  return uint4{t[0] | (t[1] << 16), t[2] | (t[3] << 16), t[4], 0u};
+  return u2v{t[0] | (t[1] << 8) | (t[2] << 16) | (t[3] << 24), t[4]};
 }
 
 // LDS byte address of this lane's table copy for byte BY of dword w:
 // bytes [slot, code, 0, 0].
 template <int BY>
-__device__ inline uint32_t q_addr(uint32_t w, uint32_t slot) {
+__device__ inline uint32_t lut_addr(uint32_t w, uint32_t slot) {
   return __builtin_amdgcn_perm(slot, w, 0x0C0C0004u | (BY << 8));
 }
 
-// Window u (inputs 8u .. 8u+7 of a group): first code byte, trit phase
-// (index of its first trit in that byte) and last code byte.
-__host__ __device__ constexpr int win_byte(int u) { return (8 * u) / 5; }
-__host__ __device__ constexpr int win_phase(int u) { return (8 * u) % 5; }
-__host__ __device__ constexpr int win_last(int u) { return (8 * u + 7) / 5; }
-
-// Table address of code byte j of a group whose bytes 0..23 are w[0..5] and
-// bytes 24, 25 the low half of w[6] (j is a constant after unrolling; w is
-// registers or a record slot in LDS).
-__device__ __attribute__((always_inline)) inline uint32_t code_byte_addr(const uint32_t* w, int j, uint32_t slot) {
-  const uint32_t word = j < 24 ? w[j >> 2] : w[6];
-  switch (j < 24 ? (j & 3) : j - 24) {
-    case 0: return q_addr<0>(word, slot);
-    case 1: return q_addr<1>(word, slot);
-    case 2: return q_addr<2>(word, slot);
-    default: return q_addr<3>(word, slot);
+// Table entries of a lane's 8 code bytes.
+__device__ __attribute__((always_inline)) inline void read_entries(const unsigned char* lut, uint32_t slot, u2v w,
+                                                                   u2v (&e)[8]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t x = h ? w.y : w.x;
+    e[4 * h] = *reinterpret_cast<const u2v*>(lut + lut_addr<0>(x, slot));
+    e[4 * h + 1] = *reinterpret_cast<const u2v*>(lut + lut_addr<1>(x, slot));
+    e[4 * h + 2] = *reinterpret_cast<const u2v*>(lut + lut_addr<2>(x, slot));
+    e[4 * h + 3] = *reinterpret_cast<const u2v*>(lut + lut_addr<3>(x, slot));
   }
 }
 
-// Table entry at LDS byte address a, read whole: a 16-byte read puts the 16
-// lanes served together on 64 different banks (one copy each), where a
-// 12-byte read is split by the compiler into reads that share banks.
-__device__ __attribute__((always_inline)) inline U3 table_entry(const unsigned char* lut, uint32_t a) {
-  const u4v v = *reinterpret_cast<const u4v*>(lut + a);
-  return U3{v.x, v.y, v.z};
-}
-
-// Patterns of a window of phase o from the table entries of its bytes: the
-// window's 8 trits are trits o..4 of e0's byte, then e1's, then e2's.
-__device__ __attribute__((always_inline)) inline void window_patterns(int o, const U3& e0, const U3& e1,
-                                                                      const U3& e2, uint32_t (&d)[4]) {
-  const uint32_t a01 = __builtin_amdgcn_alignbit(e0.y, e0.x, 16), a12 = __builtin_amdgcn_alignbit(e0.z, e0.y, 16);
-  const uint32_t b01 = __builtin_amdgcn_alignbit(e1.y, e1.x, 16), b12 = __builtin_amdgcn_alignbit(e1.z, e1.y, 16);
-  switch (o) {
-    case 0: d[0] = e0.x; d[1] = e0.y; d[2] = e0.z | (e1.x << 16); d[3] = b01; break;
-    case 1: d[0] = a01; d[1] = a12; d[2] = e1.x; d[3] = e1.y; break;
-    case 2: d[0] = e0.y; d[1] = e0.z | (e1.x << 16); d[2] = b01; d[3] = b12; break;
-    case 3: d[0] = a12; d[1] = e1.x; d[2] = e1.y; d[3] = e1.z | (e2.x << 16); break;
-    default: d[0] = e0.z | (e1.x << 16); d[1] = b01; d[2] = b12; d[3] = e2.x; break;
+// The operands of the five windows (8 trits each) from the entries.
+__device__ __attribute__((always_inline)) inline void expand(const u2v (&e)[8], u4v (&W)[5]) {
+  uint32_t d[20];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {   // two bytes: ten trits, five dwords
+    const u2v a = e[2 * p], b = e[2 * p + 1];
+    d[5 * p] = __builtin_amdgcn_perm(a.x, a.x, 0x010C000Cu);       // t0 t1
+    d[5 * p + 1] = __builtin_amdgcn_perm(a.x, a.x, 0x030C020Cu);   // t2 t3
+    d[5 * p + 2] = __builtin_amdgcn_perm(b.x, a.y, 0x040C000Cu);   // t4 t0'
+    d[5 * p + 3] = __builtin_amdgcn_perm(b.x, b.x, 0x020C010Cu);   // t1' t2'
+    d[5 * p + 4] = __builtin_amdgcn_perm(b.y, b.x, 0x040C030Cu);   // t3' t4'
   }
+#pragma unroll
+  for (int u = 0; u < 5; ++u) W[u] = u4v{d[4 * u], d[4 * u + 1], d[4 * u + 2], d[4 * u + 3]};
 }
 
-// p * s + c on two fp16 halves; p and c are fp16 bit pairs (a plain
-// uint32 must never meet a half2v by value conversion).
-__device__ inline uint32_t hfma2(uint32_t p, half2v s, uint32_t c) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(half2v, p), s,
-                                                                __builtin_bit_cast(half2v, c)));
+__device__ __attribute__((always_inline)) inline float4v mfma(u4v a, u4v b, float4v c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
 }
 
-__device__ inline half2v hsplat(uint32_t h) {
-  const _Float16 v = __builtin_bit_cast(_Float16, (uint16_t)h);
-  return half2v{v, v};
+// Holds MFMA results back until they can be read anywhere.  The compiler puts
+// wait states between an MFMA and the first read of its result, but where a
+// branch lies between the two it can count those of the longer way round
+// only (seen on an `if` directly behind a chain: the first of the four sums
+// was read too early).
+__device__ __attribute__((always_inline)) inline void settle(float4v& a, float4v& b) {
+  asm volatile("s_nop 15" : "+v"(a), "+v"(b));
 }
 
 // Workgroup barrier for LDS data only: waits for this wave's LDS accesses
@@ -170,509 +177,449 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// One plane-1 record as loaded: code bytes 0..23, bytes 24, 25, mu | s1 << 16, group.
+// A value the compiler knows nothing about: what depends on it is computed
+// here, and not ahead of the loop over chunks, where all of it would be done
+// before the first load and held in registers.
+__device__ inline int here_v(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ inline int here_s(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// One plane-1 record as loaded: code bytes 0..23, bytes 24, 25, s1 | mu << 16, group.
 struct RecLoad {
   uint64_t v0, v1, v2;
-  uint32_t tl, ms;
+  uint32_t tl, sm;
   int gg;
 };
 
-// Record k; a matrix without records reads its plane-0 arrays at k = 0
-// instead (no branch around the loads, whose results are then unused).
-__device__ inline RecLoad load_record(const MatDev& m, int64_t k) {
-  const bool has = m.nnz1 > 0;
-  const uint8_t* codes = has ? m.codes1 : m.codes0;
-  const int64_t n = has ? m.nnz1 : (int64_t)m.n_out * m.n_groups;
-  const uint16_t* mu = has ? m.offset1 : m.scale0;
-  const uint16_t* s1 = has ? m.scale1 : m.scale0;
-  const uint16_t* gi = has ? m.gidx1 : m.scale0;
-  // In bounds whatever range the caller's row pointers give.
-  k = has ? (k < 0 ? 0 : (k >= n ? n - 1 : k)) : 0;
-  const uint64_t* rm = reinterpret_cast<const uint64_t*>(codes) + 3 * k;
+// Record k (0 <= k < nnz1).
+__device__ inline RecLoad load_record(const TileArgs& a, int nnz1, int k) {
+  const uint32_t n = (uint32_t)nnz1, kk = (uint32_t)k;
+  const uint64_t* rm = reinterpret_cast<const uint64_t*>(a.codes1 + (size_t)(24u * kk));
   RecLoad r;
   r.v0 = rm[0];
   r.v1 = rm[1];
   r.v2 = rm[2];
-  r.tl = reinterpret_cast<const uint16_t*>(codes + 24 * n)[k];
-  r.ms = (uint32_t)mu[k] | ((uint32_t)s1[k] << 16);
-  r.gg = (int)gi[k];
+  r.tl = *reinterpret_cast<const uint16_t*>(a.codes1 + (size_t)(24u * n + 2u * kk));
+  r.sm = (uint32_t)a.scale1[kk] | ((uint32_t)a.offset1[kk] << 16);
+  r.gg = (int)a.gidx1[kk];
   return r;
 }
 
-// kHost: the workgroup's record range comes from the kernel arguments
-// (host row pointers), so its record loads are issued before anything else.
-template <int RT, int CT, int QPW, bool kHost>
-__global__ void __launch_bounds__(kQThreads) quad_kernel(QArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char lut[kQLutBytes];
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  constexpr int R = 16 * RT;
-  // X is loaded in bursts of L consecutive chunks per lane, a whole 128-byte
-  // line, so every line is fetched once and used whole.  Single 16-byte
-  // chunks per step made each line be refetched for every chunk: the 16
-  // batch rows of a step lie a power-of-two stride apart and evict each
-  // other from L1.  With up to two column tiles the next burst is loaded
-  // while the current one is used (NB = 2 buffers).  Three or four column
-  // tiles leave registers for one line buffer only: with several quads per
-  // wave it is refilled after each block (whole lines, the latency exposed
-  // once per 8 steps); with one quad, half-line bursts in two buffers are
-  // faster (gate 12288x4096 at B = 64: 28 against 31 us; down 4096x12288:
-  // 57 against 55 us the other way round).
-  constexpr int L = (CT <= 2 || QPW >= 2) ? 8 : 4;
-  constexpr int NB = (CT <= 2 || QPW == 1) ? 2 : 1;
-  constexpr int NW = QPW * kWindows;      // k-steps of this wave
+// RT, CT: row tiles of the workgroup, column tiles of the batch.  kRec: the
+// matrix has records.
+template <int RT, int CT, bool kRec>
+__global__ void __launch_bounds__(kThreads)
+tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ scale0, const uint16_t* __restrict__ X,
+            const int32_t* __restrict__ rowptr1, int n_out, int G, int B, int opts, int nnz1, const TileArgs a) {
+  // The table is the kernel's only static array, so it sits at LDS address 0
+  // and the byte-to-address v_perm is the whole address.
+  __shared__ __attribute__((aligned(16))) unsigned char lut[kLutBytes];
+  extern __shared__ __attribute__((aligned(32))) unsigned char lds[];
+  constexpr int NW = kWaves;
+  constexpr bool kLean = RT * CT >= 12;
+  constexpr bool kTight = RT > 1 && CT > 1;   // keep the scheduler from holding more in registers than there are
+  constexpr int R = 16 * RT, T = kThreads;
+  constexpr int kMaxC = kMaxPairs / R;
+  constexpr int kPadC = kMaxC > 64 ? 128 : (kMaxC > 32 ? 64 : 32);
+  constexpr int kWordLoads = (R * kPadC + T - 1) / T;   // staged pairs per thread
 
-  const MatDev& m = a.m;
-  const int G = m.n_groups;
-  const int64_t K = (int64_t)G * kGroup;
+  // opts: the chunk's groups, log2 of the staging threads per row (at least
+  // as many), fp32 output, offsets on every group,
+  // record ranges in the arguments.
+  const int chunk = opts & 0x1FF, bits = (opts >> 9) & 7;
+  const bool out_f32 = (opts >> 12) & 1, has_off = (opts >> 13) & 1;
+  const int K = G * kGroup;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int q = lane >> 4;                // group of the quad (A and B operands)
-  const int r16 = lane & 15;              // A: row of the tile; B: batch column
-  const uint32_t slot = (uint32_t)r16 << 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4;                // lane block: code bytes 8q.. of the group
+  const int n16 = lane & 15;              // batch row of the X operand; weight row of the W operand and of C
+  const uint32_t slot = (uint32_t)(lane & (kLutCopies - 1)) << 3;
   const int row0 = blockIdx.x * R;
-  const int nrows = min(R, m.n_out - row0);
-  const int64_t ngroups = (int64_t)m.n_out * G;
-  const bool has_off = m.offset0 != nullptr;
-  const bool has_rec = m.nnz1 > 0;
+  const int nrows = min(R, n_out - row0);
+  const uint32_t f0 = (uint32_t)row0 * (uint32_t)G;   // the workgroup's first group
 
-  int* rowptr_s = reinterpret_cast<int*>(lds);
-  uint8_t* flag_s = lds + q_flag_off(R);
-  uint4* rec_s = reinterpret_cast<uint4*>(lds + q_rec_off(R, G));
-
-  // ---- 1. Loads, all issued before any wait, every one unconditional at a
-  // clamped address (a load whose destination is also written on another
-  // path forces an early wait).  With host ranges: the workgroup's first
-  // records (their range is known), the row pointers, the first X burst,
-  // then the codes and scales of every (row tile, quad) of this wave, so the
-  // record staging waits for the records alone while the codes stream in.
-  // Without: row pointers, codes, X, then the records once the device row
-  // pointers give their range.
-  const int32_t* rp_src = has_rec ? m.rowptr1 : reinterpret_cast<const int32_t*>(m.codes0);
-  int kb = 0, ke = 0;
-  RecLoad rec0;
-  if constexpr (kHost) {
-    kb = a.rec_begin[blockIdx.x];
-    ke = a.rec_begin[blockIdx.x + 1];
-    rec0 = load_record(m, min(kb + tid, max(ke - 1, 0)));
-  }
-  const int32_t rp_l = rp_src[row0 + min(tid, nrows)];
-  const uint16_t* off_src = has_off ? m.offset0 : m.scale0;
-  const uint16_t* tail_src = reinterpret_cast<const uint16_t*>(m.codes0 + 24 * ngroups);
-
-  u4v xb[NB][L][CT];
-  auto issue_x = [&](int v) {   // burst v: k-steps v L .. v L + L - 1 of this wave
-#pragma unroll
-    for (int k = 0; k < L; ++k) {
-      const int F = v * L + k;
-      const int qi = F / kWindows, u = F % kWindows;
-      const int g = min(4 * (wave * QPW + qi) + q, G - 1);
-#pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        const int b = min(16 * c + r16, a.B - 1);
-        xb[v % NB][k][c] = *reinterpret_cast<const u4v*>(a.X + (int64_t)b * K + kGroup * g + 8 * u);
-      }
-    }
+  // X of one group and 16 batch rows: four loads of four whole rows (256
+  // bytes each), staged in the wave's LDS buffer and read back as operands:
+  // lane (q, n) and window u take the 16 bytes at 80 q + 16 u of row n, zeros
+  // for the windows that block 3 does not have.  (Loaded as operands straight
+  // from memory, every load touches 16 rows in 2 to 3 lines each: the address
+  // lookups, 40 a load, then took longer than everything else.)  Rows past B
+  // repeat the last one; their results are not stored.
+  const __amdgpu_buffer_rsrc_t xrsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<uint16_t*>(X), 0, 2 * B * K, 0x00020000);
+  const uint32_t xo = (uint32_t)q * 2u * (uint32_t)K + 16u * (uint32_t)n16;
+  // In the last column tile, whose rows may end early:
+  auto last_xo = [&](int j, int qq) {
+    return __umul24((uint32_t)min(16 * (CT - 1) + 4 * j + qq, B - 1), 2u * (uint32_t)K) + 16u * (uint32_t)n16;
   };
-  if constexpr (kHost) issue_x(0);
-
-  uint32_t cw[QPW][RT][7];   // code bytes 0..23, then bytes 24, 25
-  uint32_t sc[QPW][RT];      // s0 | offset << 16
+  uint32_t xol[4];
+  if constexpr (!kLean) {
 #pragma unroll
-  for (int qi = 0; qi < QPW; ++qi) {
-    const int g = min(4 * (wave * QPW + qi) + q, G - 1);
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int r = min(16 * rt + r16, nrows - 1);
-      const int64_t f = (int64_t)(row0 + r) * G + g;
-      const uint64_t* mp = reinterpret_cast<const uint64_t*>(m.codes0 + 24 * f);
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const uint64_t v = mp[i];
-        cw[qi][rt][2 * i] = (uint32_t)v;
-        cw[qi][rt][2 * i + 1] = (uint32_t)(v >> 32);
-      }
-      cw[qi][rt][6] = tail_src[f];
-      sc[qi][rt] = (uint32_t)m.scale0[f] | ((uint32_t)off_src[f] << 16);
-    }
+    for (int j = 0; j < 4; ++j) xol[j] = last_xo(j, q);
   }
-
-  if constexpr (!kHost) {
-    issue_x(0);
-    // The workgroup's first kQThreads plane-1 records, one per thread (a
-    // clamped in-range index where there are fewer; only threads below the
-    // count use theirs).
-    const int32_t kb_l = rp_src[row0];
-    const int32_t ke_l = rp_src[row0 + nrows];
-    kb = has_rec ? kb_l : 0;
-    ke = has_rec ? ke_l : 0;
-    rec0 = load_record(m, min(kb + tid, max(ke - 1, 0)));
-  }
-
-  // ---- 2. Table (one code and half of its copies per thread; at step k
-  // the copy index is rotated by the code so one store instruction's lanes
-  // spread over the banks), record flags cleared, row pointers.
-  for (int t = tid; t < 512; t += kQThreads) {
-    const int c = t & 255, h = t >> 8;
-    const uint4 e = q_entry(c);
+  // X of a step is turned one step ahead where the registers allow it.
+  constexpr int kXB = RT == 1 || CT == 1 ? 2 : 1;
+  auto load_x = [&](u4v (&xg)[4], int c, int g) {
 #pragma unroll
-    for (int k = 0; k < kQRep / 2; ++k)
-      reinterpret_cast<uint4*>(lut)[c * kQRep + ((8 * h + k + c) & (kQRep - 1))] = e;
-  }
-  for (int i = tid; i < (q_rec_off(R, G) - q_flag_off(R)) / 4; i += kQThreads)
-    reinterpret_cast<uint32_t*>(flag_s)[i] = 0u;
-  if (tid <= nrows) rowptr_s[tid] = rp_l;
-  lds_barrier();
-
-  // ---- 3. Plane-1 records of the workgroup's rows (CSR range kb..ke) to
-  // their (row, group) slots.
-  auto stage = [&](int k, const RecLoad& r) {
-    // Row of record k: the last r with rowptr_s[r] <= k.
-    int lo = 0, hi = nrows;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (rowptr_s[mid] <= k) lo = mid; else hi = mid;
-    }
-    if (r.gg < G) {
-      const int p = lo * G + r.gg;
-      rec_s[2 * p] = uint4{(uint32_t)r.v0, (uint32_t)(r.v0 >> 32), (uint32_t)r.v1, (uint32_t)(r.v1 >> 32)};
-      rec_s[2 * p + 1] = uint4{(uint32_t)r.v2, (uint32_t)(r.v2 >> 32), r.tl, r.ms};
-      flag_s[p] = 1;
-    }
+    for (int j = 0; j < 4; ++j)
+      xg[j] = c < CT - 1 ? __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xo, 2 * kGroup * g + (16 * c + 4 * j) * 2 * K, 0)
+                         : __builtin_amdgcn_raw_buffer_load_b128(xrsrc, kLean ? last_xo(j, here_v(q)) : xol[j], 2 * kGroup * g, 0);
   };
-  if (kb + tid < ke) stage(kb + tid, rec0);
-  for (int k = kb + kQThreads + tid; k < ke; k += kQThreads) stage(k, load_record(m, k));
-  lds_barrier();
+  unsigned char* const xw = lds + wave * 16 * kXRow + q * kXRow + 16 * n16;
+  const unsigned char* const xr0 = lds + wave * 16 * kXRow + n16 * kXRow + 80 * q;
+  const unsigned char* const xr1 = q < 3 ? xr0 : lds + tile_zero_off(NW) - 16;
+  // The wave's LDS accesses complete in order, so one buffer serves every
+  // column tile and group, without waits.
+  auto turn_x = [&](const u4v (&xg)[4], u4v (&dst)[5]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *reinterpret_cast<u4v*>(xw + 4 * j * kXRow) = xg[j];
+    __builtin_amdgcn_wave_barrier();
+    dst[0] = *reinterpret_cast<const u4v*>(xr0);
+#pragma unroll
+    for (int u = 1; u < 5; ++u) dst[u] = *reinterpret_cast<const u4v*>(xr1 + 16 * u);
+    __builtin_amdgcn_wave_barrier();
+  };
+  // Step i of a wave: column tile i % CT of its group i / CT.
+  auto load_step = [&](u4v (&xg)[4], int c, int g, int g0, int gn) {
+    const int cc = c % CT, gg = g + NW * (c / CT);
+    if (gg < gn) load_x(xg, cc, g0 + gg);
+  };
 
-  // ---- 4. Main loop: quads of this wave, 16 k-steps each, all row tiles
-  // and batch column tiles.
-  float4v acc[RT][CT];
+  // Codes 0..23 of the workgroup's rows: lane (q, n) reads bytes 8q .. 8q+7 of
+  // row n of a tile.  Block 3 (whose bytes are the tail's) and rows past the
+  // end lie outside the buffer and read as zeros.
+  const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)const_cast<uint8_t*>(codes0 + (size_t)(24u * f0)), 0, 24 * nrows * G, 0x00020000);
+  uint32_t wo[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+    wo[rt] = q < 3 ? __umul24((uint32_t)(16 * rt + n16), 24u * (uint32_t)G) + 8u * (uint32_t)q : 0x80000000u;
+  auto load_codes = [&](u2v (&dst)[RT], int g) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) dst[rt] = __builtin_amdgcn_raw_buffer_load_b64(wrsrc, wo[rt], 24 * g, 0);
+  };
+
+  float4v total[RT][CT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int c = 0; c < CT; ++c) acc[rt][c] = float4v{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < CT; ++c) total[rt][c] = float4v{0.f, 0.f, 0.f, 0.f};
 
+  for (int g0 = 0; g0 < G; g0 += chunk) {
+    // ---- 1. Loads, all issued before any wait, in the order of their use,
+    // at clamped addresses: X of the wave's first group, tails and scales;
+    // behind the table, whose set-up covers the wait for the kernel
+    // arguments, row pointers, records, offsets and the codes of the first
+    // group.  (The rest goes out behind the first barrier: a CU holds only so
+    // many loads in flight, and a wave that waits to issue one holds up the
+    // others there.)
+    const int gn = min(chunk, G - g0), glast = g0 + gn - 1;
+    u4v xg[4], xb[kXB][5];
+    u2v ring[kRing][RT];
+    load_x(xg, 0, min(g0 + wave, glast));
+    uint32_t tv[kWordLoads], sv[kWordLoads], ov[kWordLoads];
+    {
+      const int t = here_v(tid);
+      const uint8_t* tails = codes0 + (size_t)(24u * (uint32_t)n_out * (uint32_t)G) + (size_t)(2u * f0);
+      const uint16_t* scales = scale0 + (size_t)f0;
 #pragma unroll
-  for (int qi = 0; qi < QPW; ++qi) {
-    const int g = 4 * (wave * QPW + qi) + q;
-    // Per row tile: weight = p0 * s0 + c0 (+ p1 * s1 with a record), c0 =
-    // group offset + record offset (each zero where absent); lanes past the
-    // rows or groups get zero weights.
-    half2v s0v[RT], s1v[RT];
-    uint32_t c0v[RT];
-    bool hr[RT];
-    // Record codes: in registers where they fit (few column and row tiles),
-    // else read from the LDS slot when used.
-    constexpr bool kRcRegs = CT == 1 || (CT == 2 && RT <= 3);
-    uint32_t rcr[RT][kRcRegs ? 7 : 1];
-    const uint32_t* rcs[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int r = 16 * rt + r16;
-      const bool valid = g < G && r < nrows;
-      const int p = min(r, nrows - 1) * G + min(g, G - 1);
-      const uint4 rb = rec_s[2 * p + 1];
-      hr[rt] = valid && flag_s[p] != 0;
-      const float mu = hr[rt] ? h2f(rb.w & 0xFFFFu) : 0.0f;
-      const uint32_t s1b = hr[rt] ? (rb.w >> 16) : 0u;
-      const float m0 = has_off ? h2f(sc[qi][rt] >> 16) : 0.0f;
-      s0v[rt] = hsplat(valid ? (sc[qi][rt] & 0xFFFFu) : 0u);
-      const uint32_t c0 = valid ? f2h(m0 + mu) : 0u;
-      c0v[rt] = c0 | (c0 << 16);
-      s1v[rt] = hsplat(s1b);
-      rcs[rt] = reinterpret_cast<const uint32_t*>(rec_s + 2 * p);
-      if constexpr (kRcRegs) {
-        const uint4 ra = rec_s[2 * p];
-        rcr[rt][0] = ra.x; rcr[rt][1] = ra.y; rcr[rt][2] = ra.z; rcr[rt][3] = ra.w;
-        rcr[rt][4] = rb.x; rcr[rt][5] = rb.y; rcr[rt][6] = rb.z;
+      for (int j = 0; j < kWordLoads; ++j) {
+        const int r = (j * T + t) >> bits, g = (j * T + t) & ((1 << bits) - 1);
+        const uint32_t f = (uint32_t)(min(r, nrows - 1) * G + g0 + min(g, gn - 1));
+        tv[j] = *reinterpret_cast<const uint16_t*>(tails + (size_t)(2u * f));
+        sv[j] = scales[(size_t)f];
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
 
-    U3 ep0[RT], ep1[RT];   // table entry of the previous window's last byte (planes 0, 1)
+    // ---- 2. The table (once; at step k the copies' position is rotated by
+    // the code, so the lanes of a store cover the banks), and empty record
+    // lists.
+    if (g0 == 0) {
+      for (int t = here_v(tid); t < 512; t += T) {
+        const int c = t & 255, h = t >> 8;
+        const u2v e = table_entry(c);
 #pragma unroll
-    for (int v = 0; v < kWindows / L; ++v) {
-    const int F0 = qi * kWindows + v * L;
-    if (NB == 2 && F0 + L < NW) issue_x(F0 / L + 1);
+        for (int k = 0; k < kLutCopies / 4; ++k)
+          reinterpret_cast<u4v*>(lut)[c * (kLutCopies / 2) + ((8 * h + k + c) & (kLutCopies / 2 - 1))] =
+              u4v{e.x, e.y, e.x, e.y};
+      }
+      if (const int t = here_v(tid); t < 16) reinterpret_cast<uint32_t*>(lds + tile_zero_off(NW))[t] = 0u;
+    } else {
+      lds_barrier();   // the previous chunk's reads are done
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // Records of the workgroup's rows.
+    int kb = 0, ke = 0;
+    int rp = 0;   // lane r: first record of row r
+    RecLoad rec0;
+    if constexpr (kRec) {
+      const int32_t* rps = rowptr1 + row0;
+      rp = rps[min(here_v(lane), nrows)];
+      if ((opts >> 14) & 1) {   // ranges in the arguments
+        kb = a.rec_begin[blockIdx.x];
+        ke = a.rec_begin[blockIdx.x + 1];
+      } else {   // in bounds whatever the row pointers hold
+        kb = max(0, min(rps[0], nnz1));
+        ke = max(0, min(rps[nrows], nnz1));
+      }
+      rec0 = load_record(a, nnz1, max(0, min(kb + here_v(tid), ke - 1)));
+    }
+    {
+      const int t = here_v(tid);
+      const uint16_t* offs = (has_off ? a.offset0 : scale0) + (size_t)f0;   // (unused without offsets)
 #pragma unroll
-    for (int k = 0; k < L; ++k) {
-      const int u = v * L + k, F = F0 + k;
-      const u4v (&xv)[CT] = xb[(F / L) % NB][k];
-      const int j0 = win_byte(u), jl = win_last(u);
-      const bool shared = u > 0 && win_last(u - 1) == j0;   // first byte already read
+      for (int j = 0; j < kWordLoads; ++j) {
+        const int r = (j * T + t) >> bits, g = (j * T + t) & ((1 << bits) - 1);
+        ov[j] = offs[(size_t)(uint32_t)(min(r, nrows - 1) * G + g0 + min(g, gn - 1))];
+      }
+    }
+    load_codes(ring[0], min(g0 + wave, glast));
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kRec)
+      for (int i = here_v(tid); i < 4 * gn; i += T)
+        reinterpret_cast<uint32_t*>(lds + tile_count_off(NW, R, here_s(chunk)))[i] = 0u;
+    lds_barrier();
+
+    // ---- 3. Staging.
+    const int C = here_s(chunk), t = here_v(tid);
+    const int WS = tile_stride(C);
+    unsigned char* slot_s = lds + tile_slot_off(NW);
+    uint8_t* count_s = lds + tile_count_off(NW, R, C);
+    uint32_t* word_s = reinterpret_cast<uint32_t*>(lds + tile_word_off(NW, R, C));
+    uint32_t* off_s = reinterpret_cast<uint32_t*>(lds + tile_offset_off(NW, R, C));
+    if constexpr (kXB == 2) {
+      turn_x(xg, xb[0]);
+      load_step(xg, 1, wave, g0, gn);
+    }
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const U3 a0 = shared ? ep0[rt] : table_entry(lut, code_byte_addr(cw[qi][rt], j0, slot));
-        const U3 a1 = table_entry(lut, code_byte_addr(cw[qi][rt], j0 + 1, slot));
-        const U3 a2 = jl > j0 + 1 ? table_entry(lut, code_byte_addr(cw[qi][rt], jl, slot)) : a1;
-        ep0[rt] = a2;
-        uint32_t p[4], w[4];
-        window_patterns(win_phase(u), a0, a1, a2, p);
+    for (int d = 1; d < kRing; ++d) load_codes(ring[d], min(g0 + NW * d + wave, glast));
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = hfma2(p[i], s0v[rt], c0v[rt]);
-        if (hr[rt]) {
-          const uint32_t* rc = kRcRegs ? rcr[rt] : rcs[rt];
-          const U3 b0 = shared ? ep1[rt] : table_entry(lut, code_byte_addr(rc, j0, slot));
-          const U3 b1 = table_entry(lut, code_byte_addr(rc, j0 + 1, slot));
-          const U3 b2 = jl > j0 + 1 ? table_entry(lut, code_byte_addr(rc, jl, slot)) : b1;
-          ep1[rt] = b2;
-          uint32_t p1[4];
-          window_patterns(win_phase(u), b0, b1, b2, p1);
+    for (int j = 0; j < kWordLoads; ++j) {
+      const int r = (j * T + t) >> bits, g = (j * T + t) & ((1 << bits) - 1);
+      if (r < R && g < C) {
+        word_s[r * WS + g] = tv[j] | (sv[j] << 16);
+        if (has_off) off_s[r * WS + g] = ov[j];
+      }
+    }
+    if constexpr (kRec) {
+      auto stage_record = [&](int k, const RecLoad& r) {
+        // Row of record k: the rows after the first that start at or before
+        // it (rows past the end hold the end of the records).
+        int lo = 0;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) w[i] = hfma2(p1[i], s1v[rt], w[i]);
+        for (int r = 1; r < R; ++r) lo += k >= __builtin_amdgcn_readlane(rp, r) ? 1 : 0;
+        const int g = r.gg - g0, n = lo & 15;
+        if (k < ke && r.gg < G && g >= 0 && g < gn) {
+          // Which pass holds a record does not matter for the result: the
+          // records of a group belong to different rows.
+          const uint32_t old = atomicAdd(reinterpret_cast<uint32_t*>(count_s) + 4 * g + (n >> 2), 1u << (8 * (n & 3)));
+          const int p = (int)((old >> (8 * (n & 3))) & 0xFFu);
+          if (p < RT) {
+            u2v* d = reinterpret_cast<u2v*>(slot_s + 32 * ((g * RT + p) * 16 + n));
+            d[0] = __builtin_bit_cast(u2v, r.v0);
+            d[1] = __builtin_bit_cast(u2v, r.v1);
+            d[2] = __builtin_bit_cast(u2v, r.v2);
+            d[3] = u2v{r.tl | ((uint32_t)(lo >> 4) << 16), r.sm};
+          }
         }
-        const half8 A = __builtin_bit_cast(half8, u4v{w[0], w[1], w[2], w[3]});
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-          acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, __builtin_bit_cast(half8, xv[c]), acc[rt][c], 0, 0, 0);
-      }
+      };
+      if (kb + (t & ~63) < ke) stage_record(kb + t, rec0);
+      for (int k = kb + T; k < ke; k += T) stage_record(k + t, load_record(a, nnz1, min(k + t, ke - 1)));
     }
-    if (NB == 1 && F0 + L < NW) issue_x(F0 / L + 1);
+    lds_barrier();
+
+    // ---- 4. Main loop: this wave's groups of the chunk.
+    const int ml = here_v(lane), n16 = ml & 15, q = ml >> 4;
+    const uint32_t tail_mask = ml >= 48 ? 0xFFFFu : 0u;
+    // Staged data of a group, one group ahead where the registers allow it.
+    constexpr int SB = kTight ? 1 : 2;
+    uint32_t word[SB][RT];
+    int count[SB];
+    u2v rw[SB], re[SB];
+    auto read_staged = [&](int b, int g) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) word[b][rt] = word_s[(16 * rt + n16) * WS + g];
+      if constexpr (kRec) {
+        count[b] = count_s[16 * g + n16];
+        const unsigned char* rs = slot_s + 32 * (16 * RT * g + n16);
+        rw[b] = *reinterpret_cast<const u2v*>(rs + 8 * q);
+        re[b] = *reinterpret_cast<const u2v*>(rs + 24);
+      }
+    };
+    read_staged(0, min(wave, gn - 1));
+    // Table entries of the next tile, read before the MFMAs of the tile
+    // before it.
+    u2v e[8];
+    read_entries(lut, slot, u2v{ring[0][0].x | (word[0][0] & tail_mask), ring[0][0].y}, e);
+    for (int gb = wave; gb < gn; gb += NW * kRing) {
+#pragma unroll
+      for (int d = 0; d < kRing; ++d) {
+        const int g = gb + NW * d;
+        if (g >= gn) break;
+        if constexpr (SB == 1) read_staged(0, g);
+        else if (g + NW < gn) read_staged((d + 1) % 2, g + NW);
+        // Codes of the next group's first tile.
+        const uint32_t next_word = SB == 2 ? word[(d + 1) % SB][0] : word_s[n16 * WS + min(g + NW, gn - 1)];
+        // Row tiles, then the first pass of plane 1; their operands are
+        // decoded once, for every column tile.
+        constexpr int NT = RT + (kRec ? 1 : 0);
+        u4v W[NT][5];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          const u4v (&xv)[5] = xb[(d * CT + c) % kXB];
+          if constexpr (kXB == 2) {
+            if (c + 1 < CT || g + NW < gn) turn_x(xg, xb[(d * CT + c + 1) % 2]);
+            load_step(xg, c + 2, g, g0, gn);
+          } else {
+            turn_x(xg, xb[0]);
+            load_step(xg, c + 1, g, g0, gn);
+          }
+          float4v acc[NT], xs = {0.f, 0.f, 0.f, 0.f};
+          auto add_plane0 = [&](int rt) {
+            const float s0 = h2f(word[d % SB][rt] >> 16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) total[rt][c][i] = __builtin_fmaf(s0, acc[rt][i], total[rt][c][i]);
+          };
+          // The sum of x over the group, laid out as the totals.
+          if (kRec || has_off)
+#pragma unroll
+            for (int u = 0; u < 5; ++u) xs = mfma(xv[u], u4v{kOnes, kOnes, kOnes, kOnes}, xs);
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            if (c == 0) {
+              expand(e, W[t]);
+              if (t + 1 < RT)
+                read_entries(lut, slot, u2v{ring[d][(t + 1) % RT].x | (word[d % SB][(t + 1) % RT] & tail_mask),
+                                            ring[d][(t + 1) % RT].y}, e);
+              else if (t + 1 < NT)
+                read_entries(lut, slot, rw[d % SB], e);
+            }
+            if (c == CT - 1 && t == NT - 1) {
+              const u2v w = ring[(d + 1) % kRing][0];
+              read_entries(lut, slot, u2v{w.x | (next_word & tail_mask), w.y}, e);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < 5; ++u) acc[t] = mfma(xv[u], W[t][u], acc[t]);
+            if (t > 0) add_plane0(t - 1);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (c == 0) load_codes(ring[d], min(g0 + g + NW * kRing, glast));
+          settle(xs, acc[NT - 1]);
+          if constexpr (!kRec) add_plane0(RT - 1);
+          if (has_off) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+              const float mu = h2f(off_s[(16 * rt + n16) * WS + g]);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) total[rt][c][i] = __builtin_fmaf(mu, xs[i], total[rt][c][i]);
+            }
+          }
+          if constexpr (kRec) {
+            // Rows without a record keep their totals, also where the sums
+            // of the empty slot are not finite.
+            auto add_plane1 = [&](bool have, u2v e, const float4v& v) {
+              const float s1 = h2f(e.y & 0xFFFFu), mu = h2f(e.y >> 16);
+#pragma unroll
+              for (int rt = 0; rt < RT; ++rt)
+                if (have && (RT == 1 || (int)(e.x >> 16) == rt)) {
+#pragma unroll
+                  for (int i = 0; i < 4; ++i)
+                    total[rt][c][i] = __builtin_fmaf(s1, v[i], __builtin_fmaf(mu, xs[i], total[rt][c][i]));
+                }
+            };
+            add_plane1(count[d % SB] > 0, re[d % SB], acc[RT]);
+            if constexpr (RT > 1) {
+              for (int p = 1; p < RT; ++p) {
+                const bool have = count[d % SB] > p;
+                if (__ballot(have) == 0) break;
+                const unsigned char* rs = slot_s + 32 * ((g * RT + p) * 16 + n16);
+                float4v v = {0.f, 0.f, 0.f, 0.f};
+                const u2v w = *reinterpret_cast<const u2v*>(rs + 8 * q);
+                u2v ev[8];
+                u4v V[5];
+                if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+                read_entries(lut, slot, w, ev);
+                expand(ev, V);
+#pragma unroll
+                for (int u = 0; u < 5; ++u) v = mfma(xv[u], V[u], v);
+                settle(xs, v);
+                add_plane1(have, *reinterpret_cast<const u2v*>(rs + 24), v);
+              }
+            }
+          }
+          if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
   }
 
   // ---- 5. Partial sums of the waves, added in wave order, then Y.
-  lds_barrier();   // every wave is done with the table and the records
+  lds_barrier();   // every wave is done with the staged data
   float4v* red = reinterpret_cast<float4v*>(lds);
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int c = 0; c < CT; ++c) red[((wave * RT + rt) * CT + c) * 64 + lane] = acc[rt][c];
+    for (int c = 0; c < CT; ++c) red[((wave * RT + rt) * CT + c) * 64 + lane] = total[rt][c];
   lds_barrier();
   constexpr int kItems = RT * CT * 64;
-  for (int it = tid; it < kItems; it += kQThreads) {
-    // Four consecutive threads hold 16 consecutive rows of one column.
-    const int qq = it & 3, n = (it >> 2) & 15, c = (it >> 6) % CT, rt = (it >> 6) / CT;
-    const int ln = 16 * qq + n;
-    float4v s = red[(rt * CT + c) * 64 + ln];
+  for (int it = tid; it < kItems; it += T) {
+    const int ln = it & 63, c = (it >> 6) % CT, rt = (it >> 6) / CT;
+    float4v s = red[it];
 #pragma unroll
-    for (int w = 1; w < kQWaves; ++w) s += red[((w * RT + rt) * CT + c) * 64 + ln];
-    const int b = 16 * c + n;
-    if (b < a.B) {
+    for (int w = 1; w < NW; ++w) s += red[w * kItems + it];
+    const int r = 16 * rt + (ln & 15), b = 16 * c + 4 * (ln >> 4);
+    if (r < nrows) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = 16 * rt + 4 * qq + i;
-        if (r < nrows) {
-          const int64_t o = (int64_t)b * m.n_out + row0 + r;
-          if (a.out_f32)
+      for (int i = 0; i < 4; ++i)
+        if (b + i < B) {
+          const int64_t o = (int64_t)(b + i) * n_out + row0 + r;
+          if (out_f32)
             reinterpret_cast<float*>(a.Y)[o] = s[i];
           else
             reinterpret_cast<uint16_t*>(a.Y)[o] = (uint16_t)f2h(s[i]);
         }
-      }
     }
   }
 }
 
-// ---------------------------------------------------------------------------
-// Fallback for shapes past the quad kernel's limits: per 128-wide K step, 64
-// rows are decoded into an fp16 LDS tile in a 6-slots-per-byte order (the X
-// tile uses the same order) and multiplied with MFMA for every 16-column
-// slice of the batch.
-// ---------------------------------------------------------------------------
+typedef void (*TileKernel)(const uint8_t*, const uint16_t*, const uint16_t*, const int32_t*, int, int, int, int, int,
+                           const TileArgs);
 
-constexpr int kWaves = 4;
-constexpr int kThreads = 64 * kWaves;   // fallback kernel
-constexpr int kRows = 16 * kWaves;      // W rows per workgroup
-constexpr int kSlots = 160;             // k slots per 128-wide step
-constexpr int kStride = 168;            // LDS row stride in halves
-constexpr int kMaxColTiles = TQ_MAX_BATCH / 16;
-
-
-__device__ inline int64_t byte_offset(int64_t f, int j, int64_t n) {
-  return j < kMainBytes ? f * kMainBytes + j : (int64_t)kMainBytes * n + 2 * f + (j - kMainBytes);
+template <int RT, int CT>
+TileKernel tile_pick_rec(bool rec) {
+  return rec ? tile_kernel<RT, CT, true> : tile_kernel<RT, CT, false>;
 }
 
-__global__ void __launch_bounds__(kThreads) fallback_kernel(MatDev m, const uint16_t* __restrict__ X, int B,
-                                                        void* __restrict__ Y, int out_f32) {
-  __shared__ __attribute__((aligned(16))) uint4 lut[256];
-  __shared__ __attribute__((aligned(16))) uint16_t ws[kRows * kStride];
-  __shared__ __attribute__((aligned(16))) uint16_t xs[TQ_MAX_BATCH * kStride];
-  __shared__ int recs[kRows];
-  __shared__ int cursor[kRows];
+// Most row tiles of a workgroup: the operands of a group's row tiles are kept
+// in registers for all column tiles.
+constexpr int most_row_tiles(int CT) { return CT > 1 ? 3 : 4; }
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int G = m.n_groups;
-  const int K = G * kGroup;
-  const int64_t ngroups = (int64_t)m.n_out * G;
-  const int row0 = blockIdx.x * kRows;
-  const int nrows = min(kRows, m.n_out - row0);
-  const int ncol_tiles = (B + 15) / 16;
-
-  for (int c = tid; c < 256; c += kThreads) {
-    uint4 v = {0u, 0u, 0u, 0u};
-    if (c < 243) {
-      int cc = c, t[5];
-      for (int i = 0; i < 5; ++i) {
-        t[i] = cc % 3 - 1;
-        cc /= 3;
-      }
-      v.x = q_pattern(t[0]) | (q_pattern(t[1]) << 16);
-      v.y = q_pattern(t[2]) | (q_pattern(t[3]) << 16);
-      v.z = q_pattern(t[4]);
-    }
-    lut[c] = v;
-  }
-  if (tid < kRows) cursor[tid] = (m.nnz1 > 0 && tid < nrows) ? m.rowptr1[row0 + tid] : 0;
-  // Zero the X tile once: pad slots and absent batch rows stay zero.
-  for (int i = tid; i < TQ_MAX_BATCH * kStride / 2; i += kThreads) reinterpret_cast<uint32_t*>(xs)[i] = 0u;
-  for (int i = tid; i < kRows * kStride / 2; i += kThreads) reinterpret_cast<uint32_t*>(ws)[i] = 0u;
-
-  float4v acc[kMaxColTiles];
-#pragma unroll
-  for (int c = 0; c < kMaxColTiles; ++c) acc[c] = float4v{0.f, 0.f, 0.f, 0.f};
-
-  for (int g = 0; g < G; ++g) {
-    __syncthreads();   // previous step's MFMA reads are done; cursors visible
-    if (tid < kRows) {
-      int rec = -1;
-      if (m.nnz1 > 0 && tid < nrows) {
-        const int cur = cursor[tid];
-        if (cur < m.rowptr1[row0 + tid + 1] && (int)m.gidx1[cur] == g) {
-          rec = cur;
-          cursor[tid] = cur + 1;
-        }
-      }
-      recs[tid] = rec;
-    }
-    // X tile: batch row b, code byte j -> slots 6j .. 6j+4.
-    for (int it = tid; it < B * kGroupBytes; it += kThreads) {
-      const int b = it / kGroupBytes;
-      const int j = it - b * kGroupBytes;
-      const uint16_t* xp = X + (int64_t)b * K + kGroup * g + 5 * j;
-      uint16_t* dst = xs + b * kStride + 6 * j;
-#pragma unroll
-      for (int i = 0; i < 5; ++i) dst[i] = (5 * j + i < kGroup) ? xp[i] : (uint16_t)0;
-    }
-    __syncthreads();   // recs visible
-    // W tile: row r, code byte j -> slots 6j .. 6j+5.
-    for (int it = tid; it < kRows * kGroupBytes; it += kThreads) {
-      const int r = it / kGroupBytes;
-      const int j = it - r * kGroupBytes;
-      uint32_t o0 = 0u, o1 = 0u, o2 = 0u;
-      if (r < nrows) {
-        const int64_t f = (int64_t)(row0 + r) * G + g;
-        const int c0 = m.codes0[byte_offset(f, j, ngroups)];
-        const uint16_t s0b = m.scale0[f];
-        const int k = recs[r];
-        const uint4 p = lut[c0];
-        const bool off = m.offset0 != nullptr;
-        if (k < 0 && !off) {
-          const half2v s2 = {__builtin_bit_cast(_Float16, s0b), __builtin_bit_cast(_Float16, s0b)};
-          o0 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, p.x) * s2);
-          o1 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, p.y) * s2);
-          o2 = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, p.z) * s2);
-        } else {
-          // a = +0; a += mu0; a += mu; a += s0*t0; a += s1*t1 (the terms
-          // that exist), rounded once.
-          const int c1 = k >= 0 ? m.codes1[byte_offset(k, j, m.nnz1)] : 121;
-          const float s0 = h2f(s0b);
-          const float mu0 = off ? h2f(m.offset0[f]) : 0.0f;
-          const float mu = k >= 0 ? h2f(m.offset1[k]) : 0.0f, s1 = k >= 0 ? h2f(m.scale1[k]) : 0.0f;
-          int d0 = c0, d1 = c1;
-          uint16_t h[5];
-#pragma unroll
-          for (int i = 0; i < 5; ++i) {
-            float a = 0.0f;
-            if (off) a = a + mu0;
-            if (k >= 0) a = a + mu;
-            a = a + s0 * (float)(d0 % 3 - 1);
-            if (k >= 0) a = a + s1 * (float)(d1 % 3 - 1);
-            h[i] = __builtin_bit_cast(uint16_t, (_Float16)a);
-            d0 /= 3;
-            d1 /= 3;
-          }
-          o0 = h[0] | ((uint32_t)h[1] << 16);
-          o1 = h[2] | ((uint32_t)h[3] << 16);
-          o2 = h[4];
-        }
-      }
-      uint32_t* dst = reinterpret_cast<uint32_t*>(ws + r * kStride + 6 * j);
-      dst[0] = o0;
-      dst[1] = o1;
-      dst[2] = o2;
-    }
-    __syncthreads();
-    // MFMA: this wave's 16 rows against every 16-column slice of the batch.
-    const uint16_t* arow = ws + (wave * 16 + (lane & 15)) * kStride + 8 * (lane >> 4);
-#pragma unroll
-    for (int ks = 0; ks < kSlots / 32; ++ks) {
-      const half8 a = *reinterpret_cast<const half8*>(arow + 32 * ks);
-#pragma unroll
-      for (int c = 0; c < kMaxColTiles; ++c) {
-        if (c < ncol_tiles) {
-          const uint16_t* brow = xs + (16 * c + (lane & 15)) * kStride + 8 * (lane >> 4) + 32 * ks;
-          const half8 bv = *reinterpret_cast<const half8*>(brow);
-          acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bv, acc[c], 0, 0, 0);
-        }
-      }
-    }
-  }
-
-  // acc[c][i] is C[row = 4*(lane/16) + i][col = lane % 16] of this wave's tile.
-#pragma unroll
-  for (int c = 0; c < kMaxColTiles; ++c) {
-    if (c < ncol_tiles) {
-      const int b = 16 * c + (lane & 15);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = wave * 16 + 4 * (lane >> 4) + i;
-        if (b < B && r < nrows) {
-          const int64_t o = (int64_t)b * m.n_out + row0 + r;
-          if (out_f32)
-            reinterpret_cast<float*>(Y)[o] = acc[c][i];
-          else
-            reinterpret_cast<uint16_t*>(Y)[o] = __builtin_bit_cast(uint16_t, (_Float16)acc[c][i]);
-        }
-      }
-    }
-  }
-}
-
-
-
-
-typedef void (*QKernel)(QArgs);
-
-template <int RT, int QPW, bool H>
-QKernel q_pick(int CT) {
-  switch (CT) {
-    case 1: return quad_kernel<RT, 1, QPW, H>;
-    case 2: return quad_kernel<RT, 2, QPW, H>;
-    case 3: return quad_kernel<RT, 3, QPW, H>;
-    default:
-      if constexpr (RT == 4) return nullptr;   // not launched: it would spill registers
-      else return quad_kernel<RT, 4, QPW, H>;
-  }
-}
-
-// (RT, QPW) pairs with RT * QPW <= kQMaxUnits.
-template <bool H>
-QKernel q_select(int RT, int QPW, int CT) {
+template <int CT>
+TileKernel tile_pick(int RT, bool rec) {
   switch (RT) {
-    case 1:
-      switch (QPW) {
-        case 1: return q_pick<1, 1, H>(CT);
-        case 2: return q_pick<1, 2, H>(CT);
-        case 3: return q_pick<1, 3, H>(CT);
-        default: return q_pick<1, 4, H>(CT);
-      }
-    case 2: return QPW == 1 ? q_pick<2, 1, H>(CT) : q_pick<2, 2, H>(CT);
-    case 3: return q_pick<3, 1, H>(CT);
-    default: return q_pick<4, 1, H>(CT);
+    case 1: return tile_pick_rec<1, CT>(rec);
+    case 2: return tile_pick_rec<2, CT>(rec);
+    case 3: return tile_pick_rec<3, CT>(rec);
+    default: return tile_pick_rec<most_row_tiles(CT), CT>(rec);
   }
 }
 
-struct QDeviceInfo {
-  bool attr_set[2][4][4][4] = {};
-};
-
-QDeviceInfo& q_device_info() {
-  static thread_local QDeviceInfo info[64];
+// Whether the kernel's LDS limit is raised already, per device.
+bool& tile_attr_set(TileKernel k) {
+  static thread_local std::unordered_map<const void*, bool> set[64];
   int dev = 0;
   (void)hipGetDevice(&dev);
-  return info[dev & 63];
+  return set[dev & 63][reinterpret_cast<const void*>(k)];
 }
 
 }  // namespace
@@ -680,54 +627,59 @@ QDeviceInfo& q_device_info() {
 hipError_t launch_gemm_smallbatch(const MatDev& m, const uint16_t* X, int B, void* Y, bool out_f32,
                                   hipStream_t s) {
   const int G = m.n_groups;
-  const int NQ = (G + 3) / 4;
-  const int QPW = (NQ + kQWaves - 1) / kQWaves;
-  // Rows per workgroup: about one workgroup per CU (256), at most 4 row
-  // tiles, and at most kQMaxUnits (row tile, quad) units per wave and
-  // kQMaxPairs record slots.
-  int RT = (m.n_out + 16 * 256 - 1) / (16 * 256);
-  RT = RT < 1 ? 1 : (RT > 4 ? 4 : RT);
   const int CT = (B + 15) / 16;
-  // Four row tiles with four column tiles would spill registers.
-  if (RT == 4 && CT == 4) RT = 3;
-  while (RT > 1 && (RT * QPW > kQMaxUnits || 16 * RT * G > kQMaxPairs)) --RT;
-  if (RT * QPW > kQMaxUnits || 16 * RT * G > kQMaxPairs) {
-    const int wgs = (m.n_out + kRows - 1) / kRows;
-    hipLaunchKernelGGL(fallback_kernel, dim3(wgs), dim3(kThreads), 0, s, m, X, B, Y, out_f32 ? 1 : 0);
-    return hipGetLastError();
-  }
+  // Rows per workgroup: about one workgroup per CU (256).
+  int RT = (m.n_out + 16 * 256 - 1) / (16 * 256);
+  RT = RT < most_row_tiles(CT) ? RT : most_row_tiles(CT);
   const int R = 16 * RT;
-  const int staged = q_stage_bytes(R, G);
-  const int red = q_red_bytes(RT, CT);
-  const int dyn = staged > red ? staged : red;
   const int wgs = (m.n_out + R - 1) / R;
+  // Chunks of equal size, as few as hold at most kMaxPairs pairs.
+  const int most_groups = kMaxPairs / R;
+  const int chunks = (G + most_groups - 1) / most_groups;
+  const int C = (G + chunks - 1) / chunks;
+  int lane_bits = 4;
+  while ((1 << lane_bits) < C) ++lane_bits;
+
   // Record ranges in the kernel arguments where the host has the row
-  // pointers (or there are no records) and the workgroups are few enough.
-  const bool host = (m.nnz1 == 0 || m.rowptr1_host != nullptr) && wgs <= kQMaxRanges;
-  const QKernel kern = host ? q_select<true>(RT, QPW, CT) : q_select<false>(RT, QPW, CT);
-  if (kern == nullptr) return hipErrorInvalidValue;
-  QDeviceInfo& di = q_device_info();
-  if (!di.attr_set[host][RT - 1][QPW - 1][CT - 1]) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit - kQLutBytes);
-    if (e != hipSuccess) return e;
-    di.attr_set[host][RT - 1][QPW - 1][CT - 1] = true;
+  // pointers and the workgroups are few enough.
+  const bool rec = m.nnz1 > 0;
+  const bool host = rec && m.rowptr1_host != nullptr && wgs <= kMaxRanges;
+  TileKernel kernel;
+  switch (CT) {
+    case 1: kernel = tile_pick<1>(RT, rec); break;
+    case 2: kernel = tile_pick<2>(RT, rec); break;
+    case 3: kernel = tile_pick<3>(RT, rec); break;
+    default: kernel = tile_pick<4>(RT, rec); break;
   }
-  QArgs args;
-  args.m = m;
-  args.X = X;
+  TileArgs args;
+  args.offset0 = m.offset0;
+  args.codes1 = m.codes1;
+  args.gidx1 = m.gidx1;
+  args.offset1 = m.offset1;
+  args.scale1 = m.scale1;
   args.Y = Y;
-  args.B = B;
-  args.out_f32 = out_f32 ? 1 : 0;
   if (host) {
     for (int w = 0; w <= wgs; ++w) {
       const int64_t r = (int64_t)w * R < m.n_out ? (int64_t)w * R : m.n_out;
-      int64_t v = m.nnz1 > 0 ? m.rowptr1_host[r] : 0;
+      int64_t v = m.rowptr1_host[r];
       v = v < 0 ? 0 : (v > m.nnz1 ? m.nnz1 : v);   // in bounds whatever the host copy holds
       args.rec_begin[w] = (int32_t)v;
     }
   }
-  hipLaunchKernelGGL(kern, dim3(wgs), dim3(kQThreads), dyn, s, args);
+  const int staged = tile_lds(kWaves, R, C, m.offset0 != nullptr);
+  const int red = tile_red_bytes(kWaves, RT, CT);
+  const int dyn = staged > red ? staged : red;
+  bool& set = tile_attr_set(kernel);
+  if (!set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit - kLutBytes);
+    if (e != hipSuccess) return e;
+    set = true;
+  }
+  const int opts = C | (lane_bits << 9) | (out_f32 ? 1 << 12 : 0) | (m.offset0 != nullptr ? 1 << 13 : 0) |
+                   (host ? 1 << 14 : 0);
+  hipLaunchKernelGGL(kernel, dim3(wgs), dim3(kThreads), dyn, s, m.codes0, m.scale0, X, m.rowptr1, m.n_out, G, B, opts,
+                     (int)m.nnz1, args);
   return hipGetLastError();
 }
 
