@@ -41,8 +41,6 @@
 // The waves' partial sums are added in a fixed order through LDS
 // (bit-reproducible).
 
-#include <unordered_map>
-
 #include "tq_internal.h"
 
 namespace tq {
@@ -81,8 +79,8 @@ struct TileArgs {
 // between rows so that one 16-byte read's 16 rows cover the banks; 64 zero
 // bytes; the 32-byte record slots [group][pass][16] (code bytes 0..23, tail,
 // row tile, s1 | mu << 16); a byte per (group, row % 16) with its number of
-// records; per row and group the word tail | s0 << 16 and the offset, with an
-// odd row stride so that 16 rows spread over the banks.  After the main loop
+// records; per row and group the words tail | s0 << 16 and offset, with an odd
+// row stride so that 16 rows spread over the banks.  After the main loop
 // the partial sums [waves][RT][CT][64 lanes] x 16 B overlay it.
 constexpr int kXRow = 2 * kGroup + 16;
 __host__ __device__ constexpr int tile_stride(int C) { return C | 1; }
@@ -90,15 +88,12 @@ __host__ __device__ constexpr int tile_zero_off(int NW) { return NW * 16 * kXRow
 __host__ __device__ constexpr int tile_slot_off(int NW) { return tile_zero_off(NW) + 64; }
 __host__ __device__ constexpr int tile_count_off(int NW, int R, int C) { return tile_slot_off(NW) + 32 * R * C; }
 __host__ __device__ constexpr int tile_word_off(int NW, int R, int C) { return tile_count_off(NW, R, C) + 16 * C; }
-__host__ __device__ constexpr int tile_offset_off(int NW, int R, int C) {
-  return tile_word_off(NW, R, C) + 4 * R * tile_stride(C);
-}
-__host__ __device__ constexpr int tile_lds(int NW, int R, int C, bool off) {
-  return tile_offset_off(NW, R, C) + (off ? 4 * R * tile_stride(C) : 0);
+__host__ __device__ constexpr int tile_lds(int NW, int R, int C) {
+  return tile_word_off(NW, R, C) + 8 * R * tile_stride(C);
 }
 __host__ __device__ constexpr int tile_red_bytes(int NW, int RT, int CT) { return NW * RT * CT * 64 * 16; }
-static_assert(kLutBytes + tile_lds(8, 16, 96, true) <= kLdsLimit && kLutBytes + tile_lds(8, 32, 48, true) <= kLdsLimit &&
-                  kLutBytes + tile_lds(8, 48, 32, true) <= kLdsLimit && kLutBytes + tile_lds(8, 64, 24, true) <= kLdsLimit,
+static_assert(kLutBytes + tile_lds(kWaves, 16, 96) <= kLdsLimit && kLutBytes + tile_lds(kWaves, 32, 48) <= kLdsLimit &&
+                  kLutBytes + tile_lds(kWaves, 48, 32) <= kLdsLimit && kLutBytes + tile_lds(kWaves, 64, 24) <= kLdsLimit,
               "a full chunk fits");
 
 __device__ inline float h2f(uint32_t b) { return (float)__builtin_bit_cast(_Float16, (uint16_t)b); }
@@ -177,6 +172,17 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// LDS at a byte address: the address of a loop's next access is then one
+// register with the offset in the instruction (a pointer into the dynamic
+// block, which starts behind the table, costs an add per access).
+template <typename V>
+__device__ __attribute__((always_inline)) inline V lds_read(uint32_t at) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) V*>(at);
+}
+__device__ __attribute__((always_inline)) inline uint32_t lds_address(const void* p) {
+  return (uint32_t)reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)p);
+}
+
 // A value the compiler knows nothing about: what depends on it is computed
 // here, and not ahead of the loop over chunks, where all of it would be done
 // before the first load and held in registers.
@@ -211,8 +217,10 @@ __device__ inline RecLoad load_record(const TileArgs& a, int nnz1, int k) {
 }
 
 // RT, CT: row tiles of the workgroup, column tiles of the batch.  kRec: the
-// matrix has records.
-template <int RT, int CT, bool kRec>
+// matrix has records.  kQuads: quads of rows that the last column tile of X
+// can hold (the rest of its LDS rows is left as it is: a row of X is a row of
+// the result, which nobody stores).
+template <int RT, int CT, bool kRec, int kQuads>
 __global__ void __launch_bounds__(kThreads)
 tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ scale0, const uint16_t* __restrict__ X,
             const int32_t* __restrict__ rowptr1, int n_out, int G, int B, int opts, int nnz1, const TileArgs a) {
@@ -267,7 +275,7 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
   constexpr int kXB = RT == 1 || CT == 1 ? 2 : 1;
   auto load_x = [&](u4v (&xg)[4], int c, int g) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < (c < CT - 1 ? 4 : kQuads); ++j)
       xg[j] = c < CT - 1 ? __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xo, 2 * kGroup * g + (16 * c + 4 * j) * 2 * K, 0)
                          : __builtin_amdgcn_raw_buffer_load_b128(xrsrc, kLean ? last_xo(j, here_v(q)) : xol[j], 2 * kGroup * g, 0);
   };
@@ -278,18 +286,17 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
   // column tile and group, without waits.
   auto turn_x = [&](const u4v (&xg)[4], u4v (&dst)[5]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) *reinterpret_cast<u4v*>(xw + 4 * j * kXRow) = xg[j];
+    for (int j = 0; j < (CT == 1 ? kQuads : 4); ++j) *reinterpret_cast<u4v*>(xw + 4 * j * kXRow) = xg[j];
     __builtin_amdgcn_wave_barrier();
     dst[0] = *reinterpret_cast<const u4v*>(xr0);
 #pragma unroll
     for (int u = 1; u < 5; ++u) dst[u] = *reinterpret_cast<const u4v*>(xr1 + 16 * u);
     __builtin_amdgcn_wave_barrier();
   };
-  // Step i of a wave: column tile i % CT of its group i / CT.
-  auto load_step = [&](u4v (&xg)[4], int c, int g, int g0, int gn) {
-    const int cc = c % CT, gg = g + NW * (c / CT);
-    if (gg < gn) load_x(xg, cc, g0 + gg);
-  };
+  // Step i of a wave: column tile i % CT of its group i / CT.  Steps past the
+  // chunk repeat its last group, unused: a load under a condition would make
+  // every later wait for an older load wait for it as well.
+  auto load_step = [&](u4v (&xg)[4], int c, int g, int glast) { load_x(xg, c % CT, min(g + NW * (c / CT), glast)); };
 
   // Codes 0..23 of the workgroup's rows: lane (q, n) reads bytes 8q .. 8q+7 of
   // row n of a tile.  Block 3 (whose bytes are the tail's) and rows past the
@@ -392,11 +399,10 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
     const int WS = tile_stride(C);
     unsigned char* slot_s = lds + tile_slot_off(NW);
     uint8_t* count_s = lds + tile_count_off(NW, R, C);
-    uint32_t* word_s = reinterpret_cast<uint32_t*>(lds + tile_word_off(NW, R, C));
-    uint32_t* off_s = reinterpret_cast<uint32_t*>(lds + tile_offset_off(NW, R, C));
+    u2v* word_s = reinterpret_cast<u2v*>(lds + tile_word_off(NW, R, C));
     if constexpr (kXB == 2) {
       turn_x(xg, xb[0]);
-      load_step(xg, 1, wave, g0, gn);
+      load_step(xg, 1, g0 + wave, glast);
     }
 #pragma unroll
     for (int d = 1; d < kRing; ++d) load_codes(ring[d], min(g0 + NW * d + wave, glast));
@@ -405,8 +411,7 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
     for (int j = 0; j < kWordLoads; ++j) {
       const int r = (j * T + t) >> bits, g = (j * T + t) & ((1 << bits) - 1);
       if (r < R && g < C) {
-        word_s[r * WS + g] = tv[j] | (sv[j] << 16);
-        if (has_off) off_s[r * WS + g] = ov[j];
+        word_s[r * WS + g] = u2v{tv[j] | (sv[j] << 16), ov[j]};
       }
     }
     if constexpr (kRec) {
@@ -441,120 +446,128 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
     const uint32_t tail_mask = ml >= 48 ? 0xFFFFu : 0u;
     // Staged data of a group, one group ahead where the registers allow it.
     constexpr int SB = kTight ? 1 : 2;
-    uint32_t word[SB][RT];
+    u2v word[SB][RT];
     int count[SB];
     u2v rw[SB], re[SB];
+    const uint32_t word_at = here_v(lds_address(word_s + n16 * WS));
+    const uint32_t count_at = here_v(lds_address(count_s + n16)), slot_at = here_v(lds_address(slot_s + 32 * n16));
     auto read_staged = [&](int b, int g) {
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) word[b][rt] = word_s[(16 * rt + n16) * WS + g];
+      for (int rt = 0; rt < RT; ++rt) word[b][rt] = lds_read<u2v>(word_at + (uint32_t)(8 * (16 * rt * WS + g)));
       if constexpr (kRec) {
-        count[b] = count_s[16 * g + n16];
-        const unsigned char* rs = slot_s + 32 * (16 * RT * g + n16);
-        rw[b] = *reinterpret_cast<const u2v*>(rs + 8 * q);
-        re[b] = *reinterpret_cast<const u2v*>(rs + 24);
+        count[b] = lds_read<uint8_t>(count_at + (uint32_t)(16 * g));
+        rw[b] = lds_read<u2v>(slot_at + (uint32_t)(512 * RT * g + 8 * q));
+        re[b] = lds_read<u2v>(slot_at + (uint32_t)(512 * RT * g + 24));
       }
     };
     read_staged(0, min(wave, gn - 1));
     // Table entries of the next tile, read before the MFMAs of the tile
     // before it.
     u2v e[8];
-    read_entries(lut, slot, u2v{ring[0][0].x | (word[0][0] & tail_mask), ring[0][0].y}, e);
+    read_entries(lut, slot, u2v{ring[0][0].x | (word[0][0].x & tail_mask), ring[0][0].y}, e);
     for (int gb = wave; gb < gn; gb += NW * kRing) {
 #pragma unroll
       for (int d = 0; d < kRing; ++d) {
         const int g = gb + NW * d;
         if (g >= gn) break;
+        if (d == 0) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
         if constexpr (SB == 1) read_staged(0, g);
-        else if (g + NW < gn) read_staged((d + 1) % 2, g + NW);
+        else read_staged((d + 1) % 2, min(g + NW, gn - 1));
         // Codes of the next group's first tile.
-        const uint32_t next_word = SB == 2 ? word[(d + 1) % SB][0] : word_s[n16 * WS + min(g + NW, gn - 1)];
-        // Row tiles, then the first pass of plane 1; their operands are
+        const uint32_t next_word = SB == 2 ? word[(d + 1) % SB][0].x : lds_read<u2v>(word_at + (uint32_t)(8 * min(g + NW, gn - 1))).x;
+        const u2v next_codes = {ring[(d + 1) % kRing][0].x | (next_word & tail_mask), ring[(d + 1) % kRing][0].y};
+        // Whether any of the group's rows has a record: 16 rows at 10 % (3.6 %)
+        // two-plane groups have none in 18 % (56 %) of the groups.
+        const bool any = kRec && __ballot(count[d % SB] > 0) != 0;
+        // The operands of the row tiles and of the first pass of plane 1 are
         // decoded once, for every column tile.
-        constexpr int NT = RT + (kRec ? 1 : 0);
-        u4v W[NT][5];
+        u4v W[RT + (kRec ? 1 : 0)][5];
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
           const u4v (&xv)[5] = xb[(d * CT + c) % kXB];
           if constexpr (kXB == 2) {
-            if (c + 1 < CT || g + NW < gn) turn_x(xg, xb[(d * CT + c + 1) % 2]);
-            load_step(xg, c + 2, g, g0, gn);
+            turn_x(xg, xb[(d * CT + c + 1) % 2]);
+            load_step(xg, c + 2, g0 + g, glast);
           } else {
             turn_x(xg, xb[0]);
-            load_step(xg, c + 1, g, g0, gn);
+            load_step(xg, c + 1, g0 + g, glast);
           }
-          float4v acc[NT], xs = {0.f, 0.f, 0.f, 0.f};
+          float4v acc[RT], xs = {0.f, 0.f, 0.f, 0.f};
           auto add_plane0 = [&](int rt) {
-            const float s0 = h2f(word[d % SB][rt] >> 16);
+            const float s0 = h2f(word[d % SB][rt].x >> 16);
 #pragma unroll
             for (int i = 0; i < 4; ++i) total[rt][c][i] = __builtin_fmaf(s0, acc[rt][i], total[rt][c][i]);
           };
-          // The sum of x over the group, laid out as the totals.
-          if (kRec || has_off)
 #pragma unroll
-            for (int u = 0; u < 5; ++u) xs = mfma(xv[u], u4v{kOnes, kOnes, kOnes, kOnes}, xs);
-#pragma unroll
-          for (int t = 0; t < NT; ++t) {
+          for (int t = 0; t < RT; ++t) {
             if (c == 0) {
               expand(e, W[t]);
               if (t + 1 < RT)
-                read_entries(lut, slot, u2v{ring[d][(t + 1) % RT].x | (word[d % SB][(t + 1) % RT] & tail_mask),
+                read_entries(lut, slot, u2v{ring[d][(t + 1) % RT].x | (word[d % SB][(t + 1) % RT].x & tail_mask),
                                             ring[d][(t + 1) % RT].y}, e);
-              else if (t + 1 < NT)
-                read_entries(lut, slot, rw[d % SB], e);
+              else if (kRec)
+                read_entries(lut, slot, any || CT > 1 ? rw[d % SB] : next_codes, e);
             }
-            if (c == CT - 1 && t == NT - 1) {
-              const u2v w = ring[(d + 1) % kRing][0];
-              read_entries(lut, slot, u2v{w.x | (next_word & tail_mask), w.y}, e);
-            }
+            if (t == RT - 1 && c == CT - 1 && (CT > 1 || !kRec)) read_entries(lut, slot, next_codes, e);
             __builtin_amdgcn_sched_barrier(0);
             acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < 5; ++u) acc[t] = mfma(xv[u], W[t][u], acc[t]);
+            for (int u = 0; u < 5; ++u) {
+              acc[t] = mfma(xv[u], W[t][u], acc[t]);
+              // The sum of x over the group, laid out as the totals (only
+              // used with records or offsets).
+              if (t == 0) xs = mfma(xv[u], u4v{kOnes, kOnes, kOnes, kOnes}, xs);
+            }
             if (t > 0) add_plane0(t - 1);
             __builtin_amdgcn_sched_barrier(0);
           }
           if (c == 0) load_codes(ring[d], min(g0 + g + NW * kRing, glast));
-          settle(xs, acc[NT - 1]);
-          if constexpr (!kRec) add_plane0(RT - 1);
+          settle(xs, acc[RT - 1]);
+          add_plane0(RT - 1);
           if (has_off) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
-              const float mu = h2f(off_s[(16 * rt + n16) * WS + g]);
+              const float mu = h2f(word[d % SB][rt].y);
 #pragma unroll
               for (int i = 0; i < 4; ++i) total[rt][c][i] = __builtin_fmaf(mu, xs[i], total[rt][c][i]);
             }
           }
-          if constexpr (kRec) {
-            // Rows without a record keep their totals, also where the sums
-            // of the empty slot are not finite.
-            auto add_plane1 = [&](bool have, u2v e, const float4v& v) {
-              const float s1 = h2f(e.y & 0xFFFFu), mu = h2f(e.y >> 16);
+          if (any) {
+            // Pass p of plane 1: the p-th record of each slot.  Rows without a
+            // record keep their totals, also where the sums of the empty slot
+            // are not finite.
+            auto add_plane1 = [&](int p, u2v r, const u4v (&V)[5]) {
+              float4v v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int u = 0; u < 5; ++u) v = mfma(xv[u], V[u], v);
+              settle(xs, v);
+              const float s1 = h2f(r.y & 0xFFFFu), mu = h2f(r.y >> 16);
 #pragma unroll
               for (int rt = 0; rt < RT; ++rt)
-                if (have && (RT == 1 || (int)(e.x >> 16) == rt)) {
+                if (count[d % SB] > p && (RT == 1 || (int)(r.x >> 16) == rt)) {
 #pragma unroll
                   for (int i = 0; i < 4; ++i)
                     total[rt][c][i] = __builtin_fmaf(s1, v[i], __builtin_fmaf(mu, xs[i], total[rt][c][i]));
                 }
             };
-            add_plane1(count[d % SB] > 0, re[d % SB], acc[RT]);
-            if constexpr (RT > 1) {
-              for (int p = 1; p < RT; ++p) {
-                const bool have = count[d % SB] > p;
-                if (__ballot(have) == 0) break;
-                const unsigned char* rs = slot_s + 32 * ((g * RT + p) * 16 + n16);
-                float4v v = {0.f, 0.f, 0.f, 0.f};
-                const u2v w = *reinterpret_cast<const u2v*>(rs + 8 * q);
-                u2v ev[8];
-                u4v V[5];
-                if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
-                read_entries(lut, slot, w, ev);
-                expand(ev, V);
-#pragma unroll
-                for (int u = 0; u < 5; ++u) v = mfma(xv[u], V[u], v);
-                settle(xs, v);
-                add_plane1(have, *reinterpret_cast<const u2v*>(rs + 24), v);
+            if constexpr (kRec) {
+              if (c == 0) {
+                expand(e, W[RT]);
+                if constexpr (CT == 1) read_entries(lut, slot, next_codes, e);
+                __builtin_amdgcn_sched_barrier(0);
               }
+              add_plane1(0, re[d % SB], W[RT]);
+            }
+            for (int p = 1; p < RT; ++p) {
+              if (__ballot(count[d % SB] > p) == 0) break;
+              const uint32_t at = slot_at + (uint32_t)(512 * (RT * g + p));
+              u2v ev[8];
+              u4v V[5];
+              if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
+              read_entries(lut, slot, lds_read<u2v>(at + (uint32_t)(8 * q)), ev);
+              expand(ev, V);
+              add_plane1(p, lds_read<u2v>(at + 24u), V);
             }
           }
           if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
@@ -595,31 +608,32 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
 typedef void (*TileKernel)(const uint8_t*, const uint16_t*, const uint16_t*, const int32_t*, int, int, int, int, int,
                            const TileArgs);
 
-template <int RT, int CT>
+template <int RT, int CT, int Q>
 TileKernel tile_pick_rec(bool rec) {
-  return rec ? tile_kernel<RT, CT, true> : tile_kernel<RT, CT, false>;
+  return rec ? tile_kernel<RT, CT, true, Q> : tile_kernel<RT, CT, false, Q>;
 }
 
 // Most row tiles of a workgroup: the operands of a group's row tiles are kept
 // in registers for all column tiles.
 constexpr int most_row_tiles(int CT) { return CT > 1 ? 3 : 4; }
 
-template <int CT>
+template <int CT, int Q>
 TileKernel tile_pick(int RT, bool rec) {
   switch (RT) {
-    case 1: return tile_pick_rec<1, CT>(rec);
-    case 2: return tile_pick_rec<2, CT>(rec);
-    case 3: return tile_pick_rec<3, CT>(rec);
-    default: return tile_pick_rec<most_row_tiles(CT), CT>(rec);
+    case 1: return tile_pick_rec<1, CT, Q>(rec);
+    case 2: return tile_pick_rec<2, CT, Q>(rec);
+    case 3: return tile_pick_rec<3, CT, Q>(rec);
+    default: return tile_pick_rec<most_row_tiles(CT), CT, Q>(rec);
   }
 }
 
-// Whether the kernel's LDS limit is raised already, per device.
-bool& tile_attr_set(TileKernel k) {
-  static thread_local std::unordered_map<const void*, bool> set[64];
+// Whether a kernel's LDS limit is raised already, by device, column tiles and
+// quads, row tiles, records.
+bool& tile_attr_set(int CT, int quads, int RT, bool rec) {
+  static thread_local bool set[64][4][3][4][2];
   int dev = 0;
   (void)hipGetDevice(&dev);
-  return set[dev & 63][reinterpret_cast<const void*>(k)];
+  return set[dev & 63][CT - 1][quads >> 1][RT - 1][rec ? 1 : 0];
 }
 
 }  // namespace
@@ -646,10 +660,14 @@ hipError_t launch_gemm_smallbatch(const MatDev& m, const uint16_t* X, int B, voi
   const bool host = rec && m.rowptr1_host != nullptr && wgs <= kMaxRanges;
   TileKernel kernel;
   switch (CT) {
-    case 1: kernel = tile_pick<1>(RT, rec); break;
-    case 2: kernel = tile_pick<2>(RT, rec); break;
-    case 3: kernel = tile_pick<3>(RT, rec); break;
-    default: kernel = tile_pick<4>(RT, rec); break;
+    // (Instances for few rows where the whole batch is few rows: a quarter of
+    // X's loads and LDS writes at B = 4.)
+    case 1:
+      kernel = B <= 4 ? tile_pick<1, 1>(RT, rec) : (B <= 8 ? tile_pick<1, 2>(RT, rec) : tile_pick<1, 4>(RT, rec));
+      break;
+    case 2: kernel = tile_pick<2, 4>(RT, rec); break;
+    case 3: kernel = tile_pick<3, 4>(RT, rec); break;
+    default: kernel = tile_pick<4, 4>(RT, rec); break;
   }
   TileArgs args;
   args.offset0 = m.offset0;
@@ -666,10 +684,10 @@ hipError_t launch_gemm_smallbatch(const MatDev& m, const uint16_t* X, int B, voi
       args.rec_begin[w] = (int32_t)v;
     }
   }
-  const int staged = tile_lds(kWaves, R, C, m.offset0 != nullptr);
+  const int staged = tile_lds(kWaves, R, C);
   const int red = tile_red_bytes(kWaves, RT, CT);
   const int dyn = staged > red ? staged : red;
-  bool& set = tile_attr_set(kernel);
+  bool& set = tile_attr_set(CT, CT > 1 || B > 8 ? 4 : (B > 4 ? 2 : 1), RT, rec);
   if (!set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit - kLutBytes);
