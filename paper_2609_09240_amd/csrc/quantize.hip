@@ -20,12 +20,17 @@
 //
 // Two launches: every group's one-plane fit (and its energy), then the
 // two-plane groups alone, one thread per record.  A thread owns one group
-// and works in fp64 with every sum taken in index order 0..127, so each
-// threshold decision and each stored value is a deterministic function of
-// the group's 128 inputs.  Sums of 128 fp16 values
-// and of their centred magnitudes are exact in fp64 for |w| < 2^10, so the
-// plane-0 decisions do not depend on the summation order at all.  The stored
-// mu, s0, s1 are rounded from fp64 to fp16 once, to nearest even.
+// and works in fp64 with every sum taken in index order 0..127 (where a sum is
+// exact, as that of 128 fp16 values is, in any order), so each threshold
+// decision and each stored value is a deterministic function of the group's
+// 128 inputs.  The stored mu, s0, s1 are rounded from fp64 to fp16 once, to
+// nearest even.
+//
+// A group's weights stay in 64 registers, two to a register, and its trits in
+// another 64 as fp16 (in LDS, two bytes a read, they cost more than the
+// arithmetic).  Waves load whole lines and hand the rows to their lanes
+// through LDS, and the trits back.  Products with a trit are exact, so a
+// product and the sum it goes into are one fma.
 
 #include "tq_internal.h"
 
@@ -35,9 +40,13 @@
 namespace tq {
 namespace {
 
-constexpr int kThreads = 128;
+constexpr int kWaves = 4;
+constexpr int kThreads = 64 * kWaves;
 constexpr int64_t kMaxBlocks = 1 << 16;
 constexpr double kThreshold = 0.75;
+constexpr int kRowBytes = 128 + 16;   // a lane's row of the exchange buffer: 16 rows cover the LDS banks once
+
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
 // fp64 -> fp16 bits, rounded once to nearest even (overflow to inf, NaN to
 // the quiet NaN 0x7E00).
@@ -72,197 +81,318 @@ __device__ inline uint16_t f64_to_f16(double d) {
 
 __device__ inline double h2d(uint32_t bits) { return (double)__builtin_bit_cast(_Float16, (uint16_t)bits); }
 
-// A thread's group lives in LDS transposed, element i of thread t at
-// [i * kThreads + t], so the lanes of a wave touch consecutive addresses:
-// the fp16 weights and the int8 trits of both supports.
-struct GroupView {
-  const uint16_t* w;
-  int8_t* t0;
-  int8_t* t1;
-  int tid;
-  __device__ double wat(int i) const { return h2d(w[i * kThreads + tid]); }
-  __device__ double t0at(int i) const { return (double)t0[i * kThreads + tid]; }
-  __device__ double t1at(int i) const { return (double)t1[i * kThreads + tid]; }
-};
-
-__device__ inline int8_t threshold(double v, double delta) { return v > delta ? 1 : (v < -delta ? -1 : 0); }
-
 __device__ inline double ls_ratio(double num, int n) { return n > 0 ? num / (double)n : 0.0; }
 
-// Writes 128 int8 trits (16-byte aligned destination) from the transposed
-// LDS copy.
-__device__ inline void store_trits(int8_t* dst, const int8_t* t, int tid) {
+// Element i of a row of packed halves.
+__device__ __attribute__((always_inline)) inline uint32_t half_bits(const uint32_t (&v)[64], int i) {
+  return (v[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+}
+__device__ __attribute__((always_inline)) inline double at(const uint32_t (&v)[64], int i) { return h2d(v[i >> 1] >> (16 * (i & 1))); }
+
+// A pass over a group's elements in index order.  The registers it reads are
+// made opaque first, and the scheduler is held to eight elements at a time:
+// left alone, the compiler keeps every element's conversion to fp64 from one
+// pass to the next (twice the register file) or starts them all at once.
+__device__ __attribute__((always_inline)) inline void again(uint32_t (&v)[64]) {
+#pragma unroll
+  for (int i = 0; i < 64; ++i) asm volatile("" : "+v"(v[i]));
+}
+// `sum` (and the trits written, where given) end eight elements and begin the
+// next eight.
+template <typename F>
+__device__ __attribute__((always_inline)) inline void each(double& sum, F&& body) {
+#pragma unroll
+  for (int o = 0; o < kGroup; o += 8) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) body(o + i);
+    asm volatile("" : "+v"(sum));
+  }
+}
+template <typename F>
+__device__ __attribute__((always_inline)) inline void each(double& sum, uint32_t (&t)[64], F&& body) {
+#pragma unroll
+  for (int o = 0; o < kGroup; o += 8) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) body(o + i);
+    asm volatile("" : "+v"(sum), "+v"(t[o / 2]), "+v"(t[o / 2 + 1]), "+v"(t[o / 2 + 2]), "+v"(t[o / 2 + 3]));
+  }
+}
+
+// Nonzero trits of a group (both 0x3C00 and 0xBC00 have bit 13).
+__device__ __attribute__((always_inline)) inline int support(uint32_t (&t)[64]) {
+  again(t);
+  int n = 0;
+#pragma unroll
+  for (int i = 0; i < 64; ++i) n += __builtin_popcount(t[i] & 0x20002000u);
+  return n;
+}
+
+// The wave's rows: lane l gets the 256 bytes at `base` of group f, which it
+// names (any lane may name any group).  Every load instruction takes eight
+// half rows, whole lines each.
+__device__ __attribute__((always_inline)) inline void load_rows(uint32_t (&v)[64], const uint16_t* __restrict__ w,
+                                                                int64_t f, unsigned char* lds, int lane) {
+  u4v in[2][8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int64_t r = __shfl(f, 8 * j + (lane >> 3));
+    const unsigned char* src = reinterpret_cast<const unsigned char*>(w + r * kGroup) + 16 * (lane & 7);
+    in[0][j] = *reinterpret_cast<const u4v*>(src);
+    in[1][j] = *reinterpret_cast<const u4v*>(src + 128);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      *reinterpret_cast<u4v*>(lds + (8 * j + (lane >> 3)) * kRowBytes + 16 * (lane & 7)) = in[h][j];
+    __builtin_amdgcn_wave_barrier();   // (a wave's LDS accesses complete in order)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const u4v x = *reinterpret_cast<const u4v*>(lds + lane * kRowBytes + 16 * j);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[32 * h + 4 * j + k] = x[k];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Trits as int8 from packed fp16 (+1 = 0x3C00, -1 = 0xBC00, 0) to row r of
+// `out`, which the lane names (r < 0: not stored), whole lines again.
+__device__ __attribute__((always_inline)) inline void store_trits(int8_t* __restrict__ out, const uint32_t (&t)[64],
+                                                                  int64_t r, unsigned char* lds, int lane) {
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
-    uint32_t wds[4];
+    u4v x;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      uint32_t v = 0;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) v |= (uint32_t)(uint8_t)t[(16 * c + 4 * k + b) * kThreads + tid] << (8 * b);
-      wds[k] = v;
+      // Bytes 1 and 3 of two words: 0x3C, 0xBC or 0.  0x3C -> 0x01: bit 2
+      // moved to bit 0; 0xBC -> 0xFF: every bit set by the sign.
+      const uint32_t b = __builtin_amdgcn_perm(t[8 * c + 2 * k + 1], t[8 * c + 2 * k], 0x07050301u);
+      const uint32_t one = (b >> 2) & 0x01010101u, neg = (b >> 7) & 0x01010101u;
+      x[k] = one | (neg * 0xFFu);
     }
-    reinterpret_cast<uint4*>(dst)[c] = make_uint4(wds[0], wds[1], wds[2], wds[3]);
+    *reinterpret_cast<u4v*>(lds + lane * kRowBytes + 16 * c) = x;
   }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const u4v x = *reinterpret_cast<const u4v*>(lds + (8 * j + (lane >> 3)) * kRowBytes + 16 * (lane & 7));
+    const int64_t to = __shfl(r, 8 * j + (lane >> 3));
+    if (to >= 0) *reinterpret_cast<u4v*>(out + to * kGroup + 16 * (lane & 7)) = x;
+  }
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Loads group f into this thread's LDS column.
-__device__ inline void load_group(uint16_t* w_s, const uint16_t* __restrict__ w, int64_t f, int tid) {
-  const uint4* src = reinterpret_cast<const uint4*>(w + f * kGroup);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const uint4 v = src[c];
-    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w_s[(8 * c + k) * kThreads + tid] = (uint16_t)(d[k >> 1] >> (16 * (k & 1)));
-  }
+// Trits of v > delta (+1), v < -delta (-1) as fp16 bits.
+__device__ inline uint32_t trit_bits(double v, double delta) {
+  const uint32_t sign = (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 48) & 0x8000u;
+  return fabs(v) > delta ? 0x3C00u | sign : 0u;
 }
 
-// Pass 1, every group: the one-plane fit (stored for one-plane groups) and
-// its residual energy.  A two-plane group instead leaves its own index in
-// the first 8 bytes of its record's t1 row, which pass 2 reads and then
+// The largest fp16 not above d (d >= 0; NaN gives bits above every number):
+// an fp16 magnitude is above d exactly where its bits are above these.
+__device__ inline uint32_t floor_half(double d) {
+  if (d != d) return 0x7FFFu;
+  const auto c = __builtin_amdgcn_cvt_pkrtz((float)d, 0.0f);   // (float)d may have been rounded up past an fp16
+  const uint32_t b = __builtin_bit_cast(uint32_t, c) & 0xFFFFu;
+  return h2d(b) > d ? b - 1u : b;
+}
+
+// Pass 1, every group: the one-plane fit and its residual energy.  Two-plane
+// groups are stored too (pass 2 stores them again) and leave their index in
+// the first 8 bytes of their record's t1 row, which pass 2 reads and then
 // overwrites, so pass 2 can run over the records alone (no wave then mixes
-// the two fits).
-__global__ void __launch_bounds__(kThreads) one_plane_kernel(const uint16_t* __restrict__ w, int64_t n,
+// the two fits).  kOff: with an offset on every group.
+template <bool kOff>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 3))) one_plane_kernel(const uint16_t* __restrict__ w, int64_t n,
                                                              const int32_t* __restrict__ rec_index, int64_t nnz,
                                                              int iters, int8_t* __restrict__ t0_out,
                                                              uint16_t* __restrict__ s0_out, int8_t* __restrict__ t1_out,
                                                              uint16_t* __restrict__ off0_out,
                                                              double* __restrict__ energy_out) {
-  __shared__ uint16_t w_s[kGroup * kThreads];
-  __shared__ int8_t t0_s[kGroup * kThreads];
-  const int tid = threadIdx.x;
-  const GroupView g{w_s, t0_s, nullptr, tid};
+  __shared__ __attribute__((aligned(16))) unsigned char rows[kWaves][64 * kRowBytes];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  unsigned char* lds = rows[wave];
   const int64_t stride = (int64_t)gridDim.x * kThreads;
-  // Threads share no LDS data (each reads back only its own column), so no
-  // barrier is needed.
-  for (int64_t f = (int64_t)blockIdx.x * kThreads + tid; f < n; f += stride) {
-    load_group(w_s, w, f, tid);
+  // Waves share no LDS data, so no workgroup barrier is needed.
+  for (int64_t base = (int64_t)blockIdx.x * kThreads + 64 * wave; base < n; base += stride) {
+    const bool have = base + lane < n;
+    const int64_t f = have ? base + lane : n - 1;
+    uint32_t x[64], t[64];
+    load_rows(x, w, f, lds, lane);
     int64_t k = rec_index != nullptr ? (int64_t)rec_index[f] : -1;
-    if (k >= nnz) k = -1;
-    // Without group offsets mu stays 0 (the raw weights are thresholded);
-    // with them mu starts at the mean and is refined with s0.
-    double mu = 0.0;
-    if (off0_out != nullptr) {
-      double sw = 0.0;
-      for (int i = 0; i < kGroup; ++i) sw = sw + g.wat(i);
+    double mu = 0.0, s0, e = 0.0;
+    if constexpr (!kOff) {
+      // The raw weights are thresholded.  Their sums are exact in fp64 (47
+      // bits), and the sign of a weight is that of its trit: magnitudes do.
+      double sabs = 0.0;
+      again(x);
+      each(sabs, [&](int i) { sabs = sabs + fabs(at(x, i)); });
+      const uint32_t thr = floor_half(kThreshold * (sabs / kGroup));
+      double num = 0.0;
+      again(x);
+      each(num, t, [&](int i) {
+        const uint32_t h = half_bits(x, i), m = h & 0x7FFFu;
+        const bool c = m > thr;
+        num = num + h2d(c ? m : 0u);
+        const uint32_t b = c ? 0x3C00u | (h & 0x8000u) : 0u;
+        if (i & 1) t[i >> 1] |= b << 16;
+        else t[i >> 1] = b;
+      });
+      s0 = ls_ratio(num, support(t));
+      if (energy_out != nullptr) {
+        again(x);
+        again(t);
+        each(e, [&](int i) {
+          const double d = fabs(at(x, i)) - (half_bits(t, i) != 0u ? s0 : 0.0);
+          e = e + d * d;
+        });
+      }
+    } else {
+      double sw = 0.0;   // exact in any order
+      again(x);
+      each(sw, [&](int i) { sw = sw + at(x, i); });
       mu = sw / kGroup;
-    }
-    const double mu_c = mu;
-    double sabs = 0.0;
-    for (int i = 0; i < kGroup; ++i) sabs = sabs + fabs(g.wat(i) - mu_c);
-    const double delta = kThreshold * (sabs / kGroup);
-    int n_one = 0;
-    double num = 0.0;
-    for (int i = 0; i < kGroup; ++i) {
-      const double v = g.wat(i) - mu_c;
-      const int8_t t = threshold(v, delta);
-      t0_s[i * kThreads + tid] = t;
-      n_one += t != 0;
-      num = num + (double)t * v;
-    }
-    double s0_one = ls_ratio(num, n_one);
-    if (off0_out != nullptr) {
+      const double mu_c = mu;
+      double sabs = 0.0;
+      again(x);
+      each(sabs, [&](int i) { sabs = sabs + fabs(at(x, i) - mu_c); });
+      const double delta = kThreshold * (sabs / kGroup);
+      double num = 0.0;
+      again(x);
+      each(num, t, [&](int i) {
+        const double v = at(x, i) - mu_c;
+        const uint32_t b = trit_bits(v, delta);
+        if (i & 1) t[i >> 1] |= b << 16;
+        else t[i >> 1] = b;
+        num = num + (b != 0u ? fabs(v) : 0.0);
+      });
+      const int n_one = support(t);
+      s0 = ls_ratio(num, n_one);
       for (int it = 0; it < iters; ++it) {
         double a = 0.0;
-        for (int i = 0; i < kGroup; ++i) a = a + (g.wat(i) - s0_one * g.t0at(i));
+        again(x);
+        again(t);
+        each(a, [&](int i) { a = a + __builtin_fma(-s0, at(t, i), at(x, i)); });
         mu = a / kGroup;
         double b = 0.0;
-        for (int i = 0; i < kGroup; ++i) b = b + g.t0at(i) * (g.wat(i) - mu);
-        s0_one = ls_ratio(b, n_one);
+        again(x);
+        again(t);
+        each(b, [&](int i) { b = __builtin_fma(at(t, i), at(x, i) - mu, b); });
+        s0 = ls_ratio(b, n_one);
+      }
+      if (energy_out != nullptr) {
+        again(x);
+        again(t);
+        each(e, [&](int i) {
+          const double d = __builtin_fma(-s0, at(t, i), at(x, i) - mu);
+          e = e + d * d;
+        });
       }
     }
-    if (energy_out != nullptr) {
-      double e = 0.0;
-      for (int i = 0; i < kGroup; ++i) {
-        const double d = (g.wat(i) - mu) - s0_one * g.t0at(i);
-        e = e + d * d;
-      }
-      energy_out[f] = e;
-    }
-    if (k < 0) {
-      store_trits(t0_out + f * kGroup, t0_s, tid);
-      s0_out[f] = f64_to_f16(s0_one);
-      if (off0_out != nullptr) off0_out[f] = f64_to_f16(mu);
-    } else {
-      *reinterpret_cast<int64_t*>(t1_out + k * kGroup) = f;
+    store_trits(t0_out, t, have ? f : -1, lds, lane);
+    if (have) {
+      s0_out[f] = f64_to_f16(s0);
+      if constexpr (kOff) off0_out[f] = f64_to_f16(mu);
+      if (energy_out != nullptr) energy_out[f] = e;
+      if (k >= 0 && k < nnz) *reinterpret_cast<int64_t*>(t1_out + k * kGroup) = f;
     }
   }
 }
 
 // Pass 2, one thread per record: the two-plane fit of the group that named
 // it (a record no group names, or one named twice, is skipped).
-__global__ void __launch_bounds__(kThreads) two_plane_kernel(const uint16_t* __restrict__ w, int64_t n,
+// One wave a workgroup: 10 % of a 12288x4096 matrix are 615 waves for 1024 SIMDs.
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) two_plane_kernel(const uint16_t* __restrict__ w, int64_t n,
                                                              const int32_t* __restrict__ rec_index, int64_t nnz,
                                                              int iters, int8_t* __restrict__ t0_out,
                                                              uint16_t* __restrict__ s0_out, int8_t* __restrict__ t1_out,
                                                              uint16_t* __restrict__ mu_out, uint16_t* __restrict__ s1_out,
                                                              uint16_t* __restrict__ off0_out) {
-  __shared__ uint16_t w_s[kGroup * kThreads];
-  __shared__ int8_t t0_s[kGroup * kThreads];
-  __shared__ int8_t t1_s[kGroup * kThreads];
-  const int tid = threadIdx.x;
-  const GroupView g{w_s, t0_s, t1_s, tid};
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t k = (int64_t)blockIdx.x * kThreads + tid; k < nnz; k += stride) {
-    const int64_t f = *reinterpret_cast<const int64_t*>(t1_out + k * kGroup);
-    if (f < 0 || f >= n || (int64_t)rec_index[f] != k) continue;
-    load_group(w_s, w, f, tid);
+  __shared__ __attribute__((aligned(16))) unsigned char lds[64 * kRowBytes];
+  const int lane = threadIdx.x & 63;
+  const int64_t stride = (int64_t)gridDim.x * 64;
+  for (int64_t base = (int64_t)blockIdx.x * 64; base < nnz; base += stride) {
+    const int64_t k = base + lane < nnz ? base + lane : nnz - 1;
+    int64_t f = *reinterpret_cast<const int64_t*>(t1_out + k * kGroup);
+    bool have = base + lane < nnz && f >= 0 && f < n;
+    f = f >= 0 && f < n ? f : 0;
+    have = have && (int64_t)rec_index[f] == k;
+    uint32_t x[64], t0[64], t1[64];
+    load_rows(x, w, f, lds, lane);
 
     // Offset, centred first support, residual second support.
-    double sw = 0.0;
-    for (int i = 0; i < kGroup; ++i) sw = sw + g.wat(i);
+    double sw = 0.0;   // exact in any order
+    again(x);
+    each(sw, [&](int i) { sw = sw + at(x, i); });
     double mu = sw / kGroup;
     const double mu_c = mu;
     double sc = 0.0;
-    for (int i = 0; i < kGroup; ++i) sc = sc + fabs(g.wat(i) - mu_c);
+    again(x);
+    each(sc, [&](int i) { sc = sc + fabs(at(x, i) - mu_c); });
     const double delta0 = kThreshold * (sc / kGroup);
-    int c0 = 0;
     double n0 = 0.0;
-    for (int i = 0; i < kGroup; ++i) {
-      const double v = g.wat(i) - mu_c;
-      const int8_t t = threshold(v, delta0);
-      t0_s[i * kThreads + tid] = t;
-      c0 += t != 0;
-      n0 = n0 + (double)t * v;
-    }
+    again(x);
+    each(n0, t0, [&](int i) {
+      const double v = at(x, i) - mu_c;
+      const uint32_t b = trit_bits(v, delta0);
+      if (i & 1) t0[i >> 1] |= b << 16;
+      else t0[i >> 1] = b;
+      n0 = n0 + (b != 0u ? fabs(v) : 0.0);
+    });
+    const int c0 = support(t0);
     double s0 = ls_ratio(n0, c0);
     const double s0_c = s0;
     double sr = 0.0;
-    for (int i = 0; i < kGroup; ++i) sr = sr + fabs((g.wat(i) - mu_c) - s0_c * g.t0at(i));
+    again(x);
+    again(t0);
+    each(sr, [&](int i) { sr = sr + fabs(__builtin_fma(-s0_c, at(t0, i), at(x, i) - mu_c)); });
     const double delta1 = kThreshold * (sr / kGroup);
-    int c1 = 0;
     double n1 = 0.0;
-    for (int i = 0; i < kGroup; ++i) {
-      const double v = (g.wat(i) - mu_c) - s0_c * g.t0at(i);
-      const int8_t t = threshold(v, delta1);
-      t1_s[i * kThreads + tid] = t;
-      c1 += t != 0;
-      n1 = n1 + (double)t * v;
-    }
+    again(x);
+    again(t0);
+    each(n1, t1, [&](int i) {
+      const double v = __builtin_fma(-s0_c, at(t0, i), at(x, i) - mu_c);
+      const uint32_t b = trit_bits(v, delta1);
+      if (i & 1) t1[i >> 1] |= b << 16;
+      else t1[i >> 1] = b;
+      n1 = n1 + (b != 0u ? fabs(v) : 0.0);
+    });
+    const int c1 = support(t1);
     double s1 = ls_ratio(n1, c1);
     // Refinement with the supports fixed.
     for (int it = 0; it < iters; ++it) {
       double a = 0.0;
-      for (int i = 0; i < kGroup; ++i) a = a + ((g.wat(i) - s0 * g.t0at(i)) - s1 * g.t1at(i));
+      again(x);
+      again(t0);
+      again(t1);
+      each(a, [&](int i) { a = a + __builtin_fma(-s1, at(t1, i), __builtin_fma(-s0, at(t0, i), at(x, i))); });
       mu = a / kGroup;
       double b = 0.0;
-      for (int i = 0; i < kGroup; ++i) b = b + g.t0at(i) * ((g.wat(i) - mu) - s1 * g.t1at(i));
+      again(x);
+      again(t0);
+      again(t1);
+      each(b, [&](int i) { b = __builtin_fma(at(t0, i), __builtin_fma(-s1, at(t1, i), at(x, i) - mu), b); });
       s0 = ls_ratio(b, c0);
       double c = 0.0;
-      for (int i = 0; i < kGroup; ++i) c = c + g.t1at(i) * ((g.wat(i) - mu) - s0 * g.t0at(i));
+      again(x);
+      again(t0);
+      again(t1);
+      each(c, [&](int i) { c = __builtin_fma(at(t1, i), __builtin_fma(-s0, at(t0, i), at(x, i) - mu), c); });
       s1 = ls_ratio(c, c1);
     }
-    store_trits(t0_out + f * kGroup, t0_s, tid);
-    s0_out[f] = f64_to_f16(s0);
-    store_trits(t1_out + k * kGroup, t1_s, tid);
-    if (off0_out != nullptr) {   // the offset belongs to the group; the record's is 0
-      off0_out[f] = f64_to_f16(mu);
-      mu_out[k] = 0;
-    } else {
-      mu_out[k] = f64_to_f16(mu);
+    store_trits(t0_out, t0, have ? f : -1, lds, lane);
+    store_trits(t1_out, t1, have ? k : -1, lds, lane);
+    if (have) {
+      s0_out[f] = f64_to_f16(s0);
+      if (off0_out != nullptr) {   // the offset belongs to the group; the record's is 0
+        off0_out[f] = f64_to_f16(mu);
+        mu_out[k] = 0;
+      } else {
+        mu_out[k] = f64_to_f16(mu);
+      }
+      s1_out[k] = f64_to_f16(s1);
     }
-    s1_out[k] = f64_to_f16(s1);
   }
 }
 
@@ -271,17 +401,18 @@ __global__ void __launch_bounds__(kThreads) two_plane_kernel(const uint16_t* __r
 hipError_t launch_ternarize(const uint16_t* w, int64_t n, const int32_t* rec_index, int64_t nnz, int iters,
                             int8_t* t0, uint16_t* s0, int8_t* t1, uint16_t* mu, uint16_t* s1, uint16_t* off0,
                             double* energy, hipStream_t s) {
-  auto blocks_for = [](int64_t work) {
-    const int64_t b = (work + kThreads - 1) / kThreads;
+  auto blocks_for = [](int64_t work, int threads) {
+    const int64_t b = (work + threads - 1) / threads;
     return (unsigned)(b < 1 ? 1 : (b > kMaxBlocks ? kMaxBlocks : b));
   };
   const bool two = rec_index != nullptr && nnz > 0;
-  hipLaunchKernelGGL(one_plane_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s, w, n, two ? rec_index : nullptr,
+  const auto one = off0 != nullptr ? one_plane_kernel<true> : one_plane_kernel<false>;
+  hipLaunchKernelGGL(one, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, s, w, n, two ? rec_index : nullptr,
                      two ? nnz : 0, iters, t0, s0, t1, off0, energy);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !two) return e;
-  hipLaunchKernelGGL(two_plane_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, s, w, n, rec_index, nnz, iters, t0,
-                     s0, t1, mu, s1, off0);
+  hipLaunchKernelGGL(two_plane_kernel, dim3(blocks_for(nnz, 64)), dim3(64), 0, s, w, n, rec_index, nnz, iters, t0, s0,
+                     t1, mu, s1, off0);
   return hipGetLastError();
 }
 
