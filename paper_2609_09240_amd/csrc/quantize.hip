@@ -47,6 +47,8 @@ constexpr double kThreshold = 0.75;
 constexpr int kRowBytes = 128 + 16;   // a lane's row of the exchange buffer: 16 rows cover the LDS banks once
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
 
 // fp64 -> fp16 bits, rounded once to nearest even (overflow to inf, NaN to
 // the quiet NaN 0x7E00).
@@ -156,8 +158,10 @@ __device__ __attribute__((always_inline)) inline void load_rows(uint32_t (&v)[64
   }
 }
 
-// Trits as int8 from packed fp16 (+1 = 0x3C00, -1 = 0xBC00, 0) to row r of
-// `out`, which the lane names (r < 0: not stored), whole lines again.
+// Trits as int8 to row r of `out`, which the lane names (r < 0: not stored),
+// whole lines again.  kFp16: they come as fp16 bits (+1 = 0x3C00, -1 = 0xBC00,
+// 0), else as 16-bit integers.
+template <bool kFp16>
 __device__ __attribute__((always_inline)) inline void store_trits(int8_t* __restrict__ out, const uint32_t (&t)[64],
                                                                   int64_t r, unsigned char* lds, int lane) {
 #pragma unroll
@@ -165,11 +169,16 @@ __device__ __attribute__((always_inline)) inline void store_trits(int8_t* __rest
     u4v x;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      // Bytes 1 and 3 of two words: 0x3C, 0xBC or 0.  0x3C -> 0x01: bit 2
-      // moved to bit 0; 0xBC -> 0xFF: every bit set by the sign.
-      const uint32_t b = __builtin_amdgcn_perm(t[8 * c + 2 * k + 1], t[8 * c + 2 * k], 0x07050301u);
-      const uint32_t one = (b >> 2) & 0x01010101u, neg = (b >> 7) & 0x01010101u;
-      x[k] = one | (neg * 0xFFu);
+      const uint32_t lo = t[8 * c + 2 * k], hi = t[8 * c + 2 * k + 1];
+      if constexpr (kFp16) {
+        // Bytes 1 and 3 of the words: 0x3C, 0xBC or 0.  0x3C -> 0x01: bit 2
+        // moved to bit 0; 0xBC -> 0xFF: every bit set by the sign.
+        const uint32_t b = __builtin_amdgcn_perm(hi, lo, 0x07050301u);
+        const uint32_t one = (b >> 2) & 0x01010101u, neg = (b >> 7) & 0x01010101u;
+        x[k] = one | (neg * 0xFFu);
+      } else {
+        x[k] = __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+      }
     }
     *reinterpret_cast<u4v*>(lds + lane * kRowBytes + 16 * c) = x;
   }
@@ -229,17 +238,29 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
       again(x);
       each(sabs, [&](int i) { sabs = sabs + fabs(at(x, i)); });
       const uint32_t thr = floor_half(kThreshold * (sabs / kGroup));
+      // Two weights at a time in 16-bit arithmetic: m is 1 where the magnitude
+      // is above the threshold, m times the magnitude goes into the sum and m
+      // times the sign is the trit (a 12288x4096 matrix: 46 us, with energies;
+      // with a compare and selects for each weight 52).
+      const u16x2 thr2 = {(uint16_t)thr, (uint16_t)thr};
+      // Opaque, or the compiler turns min() back into compares and selects.
+      u16x2 one = {1, 1};
+      asm("" : "+v"(one));
+      u16x2 count = {0, 0};
       double num = 0.0;
       again(x);
       each(num, t, [&](int i) {
-        const uint32_t h = half_bits(x, i), m = h & 0x7FFFu;
-        const bool c = m > thr;
-        num = num + h2d(c ? m : 0u);
-        const uint32_t b = c ? 0x3C00u | (h & 0x8000u) : 0u;
-        if (i & 1) t[i >> 1] |= b << 16;
-        else t[i >> 1] = b;
+        if (i & 1) return;
+        const u16x2 mag = __builtin_bit_cast(u16x2, x[i >> 1] & 0x7FFF7FFFu);
+        const u16x2 m = __builtin_elementwise_min(__builtin_elementwise_sub_sat(mag, thr2), one);
+        count += m;
+        const uint32_t kept = __builtin_bit_cast(uint32_t, (u16x2)(mag * m));
+        num = num + h2d(kept);
+        num = num + h2d(kept >> 16);
+        const u16x2 sign = __builtin_bit_cast(u16x2, (i16x2)(__builtin_bit_cast(i16x2, x[i >> 1]) >> 15)) | one;
+        t[i >> 1] = __builtin_bit_cast(uint32_t, (u16x2)(m * sign));
       });
-      s0 = ls_ratio(num, support(t));
+      s0 = ls_ratio(num, (int)count.x + (int)count.y);
       if (energy_out != nullptr) {
         again(x);
         again(t);
@@ -290,7 +311,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
         });
       }
     }
-    store_trits(t0_out, t, have ? f : -1, lds, lane);
+    store_trits<kOff>(t0_out, t, have ? f : -1, lds, lane);
     if (have) {
       s0_out[f] = f64_to_f16(s0);
       if constexpr (kOff) off0_out[f] = f64_to_f16(mu);
@@ -381,8 +402,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       each(c, [&](int i) { c = __builtin_fma(at(t1, i), __builtin_fma(-s0, at(t0, i), at(x, i) - mu), c); });
       s1 = ls_ratio(c, c1);
     }
-    store_trits(t0_out, t0, have ? f : -1, lds, lane);
-    store_trits(t1_out, t1, have ? k : -1, lds, lane);
+    store_trits<true>(t0_out, t0, have ? f : -1, lds, lane);
+    store_trits<true>(t1_out, t1, have ? k : -1, lds, lane);
     if (have) {
       s0_out[f] = f64_to_f16(s0);
       if (off0_out != nullptr) {   // the offset belongs to the group; the record's is 0
