@@ -620,7 +620,7 @@ def main():
     paths = {
         "chain": {"us_per_step": round(ms_chain * 1e3, 2), "GBps": round(step_bytes / (ms_chain * 1e-3) / 1e9, 2),
                   "launches_per_step": 1, "kernel": "chain_kernel",
-                  "what": "tq_gemv_chain: every stage in one cooperative launch"},
+                  "what": "tq_gemv_chain: every stage in one launch"},
         "graph": {"us_per_step": round(ms_graph * 1e3, 2), "GBps": round(step_bytes / (ms_graph * 1e-3) / 1e9, 2),
                   "launches_per_step": len(launches), "kernel": "gemv_kernel",
                   "what": "one tq_gemv / tq_gemv_grouped launch per stage, captured in a HIP graph"},

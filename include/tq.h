@@ -289,8 +289,8 @@ tq_status tq_select_two_plane_noalloc(const double* energy, int64_t n_out, int32
  * computes exactly what tq_gemv_grouped(stage s) computes (bit for bit),
  * and reads its x only after every output of stage s - 1 is written, so x
  * may be (or be derived by device code in a later design from) an earlier
- * stage's output.  One cooperative launch of one 1024-thread workgroup per
- * CU runs every stage; each workgroup keeps the decode table across stages.
+ * stage's output.  One launch of one 1024-thread workgroup per CU
+ * runs every stage; each workgroup keeps the decode table across stages.
  */
 typedef struct tq_stage {
   const tq_matrix* mats;   /* host array of n matrices, all with the same n_in */

@@ -8,17 +8,26 @@
 // operation of each stage is that of tq_gemv_grouped, eq. 3).
 //
 // Design for CDNA4:
-// * One workgroup of 1024 threads per CU, all resident at once (cooperative
-//   launch), each with the 16-copy LDS table built once for the whole chain
-//   instead of once per launch.
-// * Every stage is split over the workgroups by rows (a plan built on the
-//   host: one 128-byte work record per workgroup and stage); inside a
+// * One workgroup of 1024 threads per CU, each with the 16-copy LDS table
+//   built once for the whole chain instead of once per launch.
+// * Every stage is split by rows into one item per workgroup (a plan built on
+//   the host: one 128-byte work record per item and stage); inside a
 //   workgroup the lanes own half-groups and decode exactly as the batch-1
 //   GEMV does (gemv_decode.h), so every output equals tq_gemv's bit for bit.
-// * Stage s+1 reads its x only after every workgroup has finished stage s.
-//   A workgroup writes its outputs with device-coherent stores (sc1), waits
-//   for them to complete, then publishes its own flag (one per workgroup,
-//   64 bytes apart, so no two workgroups write one cache line).  The first
+// * No cooperative launch: its cost differs with what else the device's queues
+//   hold (16 stages of 4 layers: 129 to 202 us a call, 114 without).  A workgroup
+//   takes a ticket when it starts, which is its item in stage 0.  Once all
+//   have one they all run, and each keeps its item through the stages.  Where
+//   another chain or a long kernel holds CUs that does not happen: a workgroup
+//   that has finished its first item and waits for it kDecideSpins rounds
+//   then makes the call take every further item by ticket, in stage order.
+//   An item waits for items of lower tickets alone, and those running
+//   workgroups have taken, so the chain ends however few run at a time.
+//   (Tickets in every call: 138 us.)
+// * Stage s+1 reads its x only after every item of stage s is finished.  A
+//   workgroup writes its outputs with device-coherent stores (sc1), waits
+//   for them to complete, then publishes the item's flag (one per item, 64
+//   bytes apart, so no two workgroups write one cache line).  The first
 //   wave of every workgroup polls all flags with four independent coherent
 //   loads per lane and round, and x is then read with coherent loads too:
 //   every access that crosses workgroups bypasses the non-coherent caches,
@@ -31,9 +40,9 @@
 //   two before it is computed (a wave's loads return in order, so every
 //   load issued before x delays x).
 // * Flags carry an epoch, generation * stages + stage + 1, compared modulo
-//   2^32; the last workgroup to finish a call advances the generation, so
-//   no flag is ever reset.  Every wait is bounded: past its limit a
-//   workgroup sets the sync block's sticky error word and carries on, so
+//   2^32; the last workgroup to finish a call advances the generation and
+//   puts tickets and mode back to 0, so no flag is ever reset.  Every wait is
+//   bounded: past its limit a workgroup sets the sync block's sticky error word and carries on, so
 //   the launch always ends.
 
 #include <mutex>
@@ -50,14 +59,21 @@ namespace {
 constexpr int kChainThreads = 1024;
 constexpr int kChainMaxPasses = 6;
 constexpr int kSpinLimit = 1 << 17;     // poll rounds (~0.1 s) before a wait gives up
+constexpr int kDecideSpins = 64;        // poll rounds (~50 us) for all workgroups to start
+constexpr uint32_t kOpen = 0, kFixed = 1, kTickets = 2;
 constexpr int kSyncHeadBytes = 256;
 constexpr int kFlagStrideDw = 16;       // 64 bytes between workgroup flags
+static_assert(kXTailDw + 4 <= kXStrideDw - 2, "the last two dwords of an x slot are free");
 
 struct ChainSyncHead {
   uint32_t generation;   // calls completed
   uint32_t exit_count;   // workgroups that finished the current call
   uint32_t error;        // sticky: a wait hit its limit
-  uint32_t pad[61];
+  uint32_t pad0[13];
+  uint32_t mode;         // of the current call: kOpen, kFixed or kTickets
+  uint32_t pad1[15];
+  uint32_t ticket;       // tickets taken in the current call
+  uint32_t pad2[31];
 };
 static_assert(sizeof(ChainSyncHead) == kSyncHeadBytes, "sync head size");
 
@@ -69,9 +85,13 @@ __device__ inline void st_dev(uint32_t* p, uint32_t v) {
 }
 __device__ inline bool epoch_reached(uint32_t f, uint32_t e) { return (int32_t)(f - e) >= 0; }
 
+__device__ inline uint32_t take_ticket(ChainSyncHead* head) {
+  return __hip_atomic_fetch_add(&head->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 constexpr int kCoherent = 16;   // sc1: device scope, bypassing the per-XCD caches
 
-// Wave 0 waits until every workgroup has published epoch e; then the whole
+// Wave 0 waits until every item has published epoch e; then the whole
 // workgroup proceeds.  Bounded: past kSpinLimit rounds, or once another
 // workgroup has given up, the error word is set and the wait ends.
 __device__ void wait_all(const uint32_t* flags, ChainSyncHead* head, int nwg, uint32_t e) {
@@ -139,8 +159,8 @@ constexpr int kChainAhead = 2;
 template <int kPasses>
 __device__ __attribute__((always_inline)) inline void run_stage(const ChainWork& W, const unsigned char* lut,
                                                                 unsigned char* smem, int lds_dyn, uint32_t* flags,
-                                                                ChainSyncHead* head, int nwg, uint32_t wait_e,
-                                                                uint32_t my_e) {
+                                                                ChainSyncHead* head, int nwg, int item,
+                                                                uint32_t wait_e, uint32_t my_e) {
   constexpr int T = kChainThreads;
   const int tid = threadIdx.x;
   const int G = W.G;
@@ -285,13 +305,29 @@ __device__ __attribute__((always_inline)) inline void run_stage(const ChainWork&
   // ---- 7. Publish: every output store of the workgroup has completed.
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (tid == 0) st_dev(flags + kFlagStrideDw * blockIdx.x, my_e);
+  if (tid == 0) st_dev(flags + kFlagStrideDw * item, my_e);
 }
 
-// A workgroup with no rows in a stage still keeps the chain's order.
-__device__ inline void idle_stage(uint32_t* flags, ChainSyncHead* head, int nwg, uint32_t wait_e, uint32_t my_e) {
+// An item with no rows still keeps the chain's order.
+__device__ inline void idle_stage(uint32_t* flags, ChainSyncHead* head, int nwg, int item, uint32_t wait_e,
+                                  uint32_t my_e) {
   if (wait_e != 0) wait_all(flags, head, nwg, wait_e);
-  if (threadIdx.x == 0) st_dev(flags + kFlagStrideDw * blockIdx.x, my_e);
+  if (threadIdx.x == 0) st_dev(flags + kFlagStrideDw * item, my_e);
+}
+
+// The call's mode: kFixed once the last ticket of stage 0 is taken, kTickets
+// where that takes too long.
+__device__ inline uint32_t call_mode(ChainSyncHead* head) {
+  uint32_t m = kOpen;
+  for (int spins = 0; spins < kDecideSpins && m == kOpen; ++spins) m = ld_dev(&head->mode);
+  if (m == kOpen) {
+    uint32_t was = kOpen;
+    m = __hip_atomic_compare_exchange_strong(&head->mode, &was, kTickets, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT)
+            ? kTickets
+            : was;
+  }
+  return m;
 }
 
 __global__ void __launch_bounds__(kChainThreads) __attribute__((amdgpu_waves_per_eu(4)))
@@ -301,6 +337,19 @@ chain_kernel(const ChainWork* __restrict__ plan, int32_t n_stages, unsigned char
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   ChainSyncHead* head = reinterpret_cast<ChainSyncHead*>(sync);
   uint32_t* flags = reinterpret_cast<uint32_t*>(sync + kSyncHeadBytes);
+  // Broadcast of thread 0's words, in the last dwords of the first group's x
+  // slot, which no x is staged to: the table and the dynamic LDS may fill the
+  // whole 160 KB.
+  uint32_t* word = reinterpret_cast<uint32_t*>(smem) + kXStrideDw - 2;
+  if (threadIdx.x == 0) {
+    const uint32_t t = take_ticket(head);
+    word[0] = t;
+    if (t == (uint32_t)nwg - 1) {
+      uint32_t was = kOpen;
+      __hip_atomic_compare_exchange_strong(&head->mode, &was, kFixed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
   const uint32_t gen = __builtin_amdgcn_readfirstlane(ld_dev(&head->generation));
   const uint32_t e0 = gen * (uint32_t)n_stages;
 
@@ -309,27 +358,45 @@ chain_kernel(const ChainWork* __restrict__ plan, int32_t n_stages, unsigned char
 #pragma unroll
     for (int q = 0; q < kRep; ++q) reinterpret_cast<uint4*>(lut)[c * kRep + ((q + c) & (kRep - 1))] = e;
   }
-  // The table is complete before the first stage reads it (the first
-  // stage's x barrier also orders it; this keeps idle first stages simple).
   __syncthreads();
 
-  for (int s = 0; s < n_stages; ++s) {
-    const ChainWork W = plan[(int64_t)s * nwg + blockIdx.x];
-    const uint32_t wait_e = s == 0 ? 0u : e0 + (uint32_t)s;   // epoch of stage s - 1
-    const uint32_t my_e = e0 + (uint32_t)s + 1u;
+  uint32_t mode = kOpen;
+  uint32_t t = __builtin_amdgcn_readfirstlane(word[0]);
+  for (uint32_t s = 0, first = 0;;) {
+    while (s < (uint32_t)n_stages && t - first >= (uint32_t)nwg) {
+      first += (uint32_t)nwg;
+      ++s;
+    }
+    if (s >= (uint32_t)n_stages) break;
+    const int item = (int)(t - first);
+    const ChainWork W = plan[(int64_t)t];
+    const uint32_t wait_e = s == 0 ? 0u : e0 + s;   // epoch of stage s - 1
+    const uint32_t my_e = e0 + s + 1u;
     const int passes = (W.flags >> 8) & 255;
     if (W.row_end <= W.row_begin) {
-      idle_stage(flags, head, nwg, wait_e, my_e);
-      continue;
+      idle_stage(flags, head, nwg, item, wait_e, my_e);
+    } else {
+      switch (passes) {
+        case 1: run_stage<1>(W, lut, smem, lds_dyn, flags, head, nwg, item, wait_e, my_e); break;
+        case 2: run_stage<2>(W, lut, smem, lds_dyn, flags, head, nwg, item, wait_e, my_e); break;
+        case 3: run_stage<3>(W, lut, smem, lds_dyn, flags, head, nwg, item, wait_e, my_e); break;
+        case 4: run_stage<4>(W, lut, smem, lds_dyn, flags, head, nwg, item, wait_e, my_e); break;
+        case 5: run_stage<5>(W, lut, smem, lds_dyn, flags, head, nwg, item, wait_e, my_e); break;
+        default: run_stage<6>(W, lut, smem, lds_dyn, flags, head, nwg, item, wait_e, my_e); break;
+      }
     }
-    switch (passes) {
-      case 1: run_stage<1>(W, lut, smem, lds_dyn, flags, head, nwg, wait_e, my_e); break;
-      case 2: run_stage<2>(W, lut, smem, lds_dyn, flags, head, nwg, wait_e, my_e); break;
-      case 3: run_stage<3>(W, lut, smem, lds_dyn, flags, head, nwg, wait_e, my_e); break;
-      case 4: run_stage<4>(W, lut, smem, lds_dyn, flags, head, nwg, wait_e, my_e); break;
-      case 5: run_stage<5>(W, lut, smem, lds_dyn, flags, head, nwg, wait_e, my_e); break;
-      default: run_stage<6>(W, lut, smem, lds_dyn, flags, head, nwg, wait_e, my_e); break;
+    if (mode != kFixed) {
+      __syncthreads();   // every wave has read the words
+      if (threadIdx.x == 0) {
+        const uint32_t m = mode == kOpen ? call_mode(head) : mode;
+        word[1] = m;
+        word[0] = m == kFixed ? t : take_ticket(head);
+      }
+      __syncthreads();
+      mode = __builtin_amdgcn_readfirstlane(word[1]);
+      t = __builtin_amdgcn_readfirstlane(word[0]);
     }
+    if (mode == kFixed) t += (uint32_t)nwg;
   }
 
   // The last workgroup to finish advances the generation for the next call.
@@ -339,6 +406,8 @@ chain_kernel(const ChainWork* __restrict__ plan, int32_t n_stages, unsigned char
     const uint32_t done = __hip_atomic_fetch_add(&head->exit_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (done == (uint32_t)nwg - 1) {
       st_dev(&head->exit_count, 0u);
+      st_dev(&head->ticket, 0u);
+      st_dev(&head->mode, kOpen);
       st_dev(&head->generation, gen + 1u);
     }
   }
@@ -494,9 +563,9 @@ hipError_t launch_chain(const ChainWork* plan, int n_stages, int nwg, int lds_dy
     d->attr_set = true;
   }
   unsigned char* sp = static_cast<unsigned char*>(sync);
-  void* args[] = {(void*)&plan, (void*)&n_stages, (void*)&sp, (void*)&nwg, (void*)&lds_dyn};
-  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(chain_kernel), dim3(nwg), dim3(kChainThreads), args,
-                                    (unsigned)lds_dyn, s);
+  hipLaunchKernelGGL(chain_kernel, dim3(nwg), dim3(kChainThreads), (unsigned)lds_dyn, s, plan, n_stages, sp, nwg,
+                     lds_dyn);
+  return hipGetLastError();
 }
 
 }  // namespace tq
