@@ -6,11 +6,12 @@
 // sum_i (t + 1) 3^i; bytes 0..23 of group f sit at 24 f, bytes 24..25 at
 // 24 n + 2 f (the split layout declared in tq.h).
 //
-// All of these are HBM-bound streams.  Pack and unpack give each group three
-// threads (part p owns main code bytes 8p..8p+7, part 2 also the two tail
-// bytes), so every thread moves 8 code bytes and 40-48 trit bytes with vector
-// loads and stores and consecutive lanes touch consecutive memory.  A trit
-// buffer that is not 16-byte aligned takes a one-byte-per-thread kernel.
+// All of these are HBM-bound streams.  Pack gives each group three threads
+// (part p owns main code bytes 8p..8p+7, part 2 also the two tail bytes), so
+// every thread moves 8 code bytes and 40-48 trit bytes with vector loads and
+// stores; unpack gives it eight, 16 trits each.  Consecutive lanes touch
+// consecutive memory.  A trit buffer that is not 16-byte aligned takes a
+// one-byte-per-thread kernel.
 // Validate reads the code buffer in flat 16-byte chunks.  The fp16
 // dequantisation stages blocks of rows in LDS with coalesced loads, gives
 // each thread 8-weight items and writes them with 16-byte nontemporal stores;
@@ -28,6 +29,9 @@ constexpr int64_t kMaxBlocks = 1 << 16;
 constexpr int kPartThreads = 192;   // three threads per group
 constexpr int kPartGroups = 64;     // groups per workgroup pass
 constexpr int kPartMaxBlocks = 2048;
+constexpr int kUnpackThreads = 256;   // one table entry each
+constexpr int kUnpackChunks = 4;
+constexpr int64_t kUnpackMaxBlocks = 1 << 14;
 
 constexpr int kByteThreads = 256;
 
@@ -113,80 +117,64 @@ __device__ inline uint2 trit_bytes(int c) {
   return make_uint2(lo, (uint32_t)(uint8_t)(c - 1));
 }
 
-// ORs the trit bytes e of one code into out[] at byte offset o (bytes past
-// `limit` dropped).
-template <int o, int limit>
-__device__ inline void place(uint32_t* out, uint2 e) {
-  constexpr int d = o >> 2, s = 8 * (o & 3);
-  out[d] |= e.x << s;
-  if constexpr (d + 1 < limit / 4) {
-    if constexpr (s == 0) out[d + 1] |= e.y;
-    else out[d + 1] |= (e.x >> (32 - s)) | (e.y << s);
-  }
+// Bytes above 242 in a word: b >= 243 iff its top bit is set and its low
+// seven bits plus 13 reach 128 (no carry leaves a byte).
+__device__ inline int bad_main(uint32_t w) {
+  const uint32_t t = ((w & 0x7F7F7F7Fu) + 0x0D0D0D0Du) & w & 0x80808080u;
+  return __builtin_popcount(t);
 }
 
-__global__ void __launch_bounds__(kPartThreads) unpack_kernel(const uint8_t* __restrict__ codes, int64_t n,
-                                                              int8_t* __restrict__ trits, int32_t* d_err) {
+// A thread writes 16 trits, consecutive threads consecutive 16 bytes: trits
+// 16 q .. of a group lie in the four codes from byte 16 q / 5, whose 20 trits
+// are shifted by 16 q mod 5 bytes.  Nothing crosses threads, so there is no
+// barrier behind the table's, and kUnpackChunks independent loads keep memory
+// busy (8: slower).  Memory bounds it: a 12288x4096 plane, 60 MB, takes 11.4 us
+// (5.3 TB/s), 16.6 without the nontemporal stores, and 19.3 when three threads
+// a group put the trits of 64 groups together in LDS.
+__global__ void __launch_bounds__(kUnpackThreads) unpack_kernel(const uint8_t* __restrict__ codes, int64_t n,
+                                                                int8_t* __restrict__ trits, int32_t* d_err) {
+  struct __attribute__((packed)) U32 {
+    uint32_t v;
+  };
+  typedef uint32_t u4v __attribute__((ext_vector_type(4)));
   __shared__ uint2 table[256];
-  // The pass's 64 groups of trits, written back with 16-byte lanes over
-  // consecutive addresses (per-thread stores would cut every line in pieces).
-  __shared__ uint4 tile[kPartGroups * kGroup / 16];
-  for (int c = threadIdx.x; c < 256; c += kPartThreads) table[c] = trit_bytes(c);
+  table[threadIdx.x] = trit_bytes(threadIdx.x);
   __syncthreads();
-  const int part = threadIdx.x % 3;
-  const int slot = threadIdx.x / 3;
-  uint8_t* tile_b = reinterpret_cast<uint8_t*>(tile) + slot * kGroup;
-  for (int64_t base = (int64_t)blockIdx.x * kPartGroups; base < n; base += (int64_t)gridDim.x * kPartGroups) {
-    const int64_t f = base + slot;
-    int nbad = 0;
-    if (f < n) {
-      const uint2 cw = *reinterpret_cast<const uint2*>(codes + 24 * f + 8 * part);
-      uint32_t tail = 0;
-      if (part == 2) tail = *reinterpret_cast<const uint16_t*>(codes + (int64_t)kMainBytes * n + 2 * f);
-      uint32_t cb[10];
+  const int q = threadIdx.x & 7;
+  const int first = (16 * q) / 5, o = (16 * q) % 5;
+  // Each code counts as bad once: with the first thread whose codes end in it,
+  // so a thread's fourth byte is its own only where the next starts behind it.
+  const uint32_t own = q == 4 || q == 7 ? 0xFFFFFFFFu : 0x00FFFFFFu;
+  const uint8_t* body = codes + (q < 7 ? first : 20);
+  const uint8_t* tail = codes + (int64_t)kMainBytes * n;
+  const int64_t chunks = n * (kGroup / 16);
+  constexpr int kStep = kUnpackThreads * kUnpackChunks;
+  int nbad = 0;
+  for (int64_t base = (int64_t)blockIdx.x * kStep; base < chunks; base += (int64_t)gridDim.x * kStep) {
+    uint32_t w[kUnpackChunks], t[kUnpackChunks];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        cb[i] = (cw.x >> (8 * i)) & 0xFFu;
-        cb[4 + i] = (cw.y >> (8 * i)) & 0xFFu;
-      }
-      cb[8] = tail & 0xFFu;
-      cb[9] = tail >> 8;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) nbad += cb[i] > 242u;
-      if (part == 2) nbad += (cb[8] > 242u) + (cb[9] > 242u);
-      uint32_t out[12] = {};
-      place<0, 48>(out, table[cb[0]]);
-      place<5, 48>(out, table[cb[1]]);
-      place<10, 48>(out, table[cb[2]]);
-      place<15, 48>(out, table[cb[3]]);
-      place<20, 48>(out, table[cb[4]]);
-      place<25, 48>(out, table[cb[5]]);
-      place<30, 48>(out, table[cb[6]]);
-      place<35, 48>(out, table[cb[7]]);
-      if (part == 1) {   // trits 40..79
-        *reinterpret_cast<uint2*>(tile_b + 40) = make_uint2(out[0], out[1]);
-        *reinterpret_cast<uint4*>(tile_b + 48) = make_uint4(out[2], out[3], out[4], out[5]);
-        *reinterpret_cast<uint4*>(tile_b + 64) = make_uint4(out[6], out[7], out[8], out[9]);
-      } else if (part == 0) {   // trits 0..39
-        *reinterpret_cast<uint4*>(tile_b) = make_uint4(out[0], out[1], out[2], out[3]);
-        *reinterpret_cast<uint4*>(tile_b + 16) = make_uint4(out[4], out[5], out[6], out[7]);
-        *reinterpret_cast<uint2*>(tile_b + 32) = make_uint2(out[8], out[9]);
-      } else {   // trits 80..127: bytes 24 (5 trits) and 25 (3 trits) fill 40..47
-        place<40, 48>(out, table[cb[8]]);
-        place<45, 48>(out, table[cb[9]]);
-        *reinterpret_cast<uint4*>(tile_b + 80) = make_uint4(out[0], out[1], out[2], out[3]);
-        *reinterpret_cast<uint4*>(tile_b + 96) = make_uint4(out[4], out[5], out[6], out[7]);
-        *reinterpret_cast<uint4*>(tile_b + 112) = make_uint4(out[8], out[9], out[10], out[11]);
-      }
+    for (int i = 0; i < kUnpackChunks; ++i) {
+      const int64_t c = base + i * kUnpackThreads + threadIdx.x;
+      const int64_t f = (c < chunks ? c : chunks - 8 + q) >> 3;
+      w[i] = reinterpret_cast<const U32*>(body + kMainBytes * f)->v;
+      t[i] = *reinterpret_cast<const uint16_t*>(tail + 2 * f);
     }
-    count_errors(d_err, nbad);
-    __syncthreads();
-    const int64_t left = n - base;
-    const int chunks = (int)(left < kPartGroups ? left : kPartGroups) * (kGroup / 16);
-    uint4* dst = reinterpret_cast<uint4*>(trits + base * kGroup);
-    for (int i = threadIdx.x; i < chunks; i += kPartThreads) dst[i] = tile[i];
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kUnpackChunks; ++i) {
+      const int64_t c = base + i * kUnpackThreads + threadIdx.x;
+      const uint32_t x = q < 7 ? w[i] : (w[i] >> 16) | (t[i] << 16);
+      if (c < chunks) nbad += bad_main(x & own);
+      const uint2 e0 = table[x & 0xFFu], e1 = table[(x >> 8) & 0xFFu], e2 = table[(x >> 16) & 0xFFu], e3 = table[x >> 24];
+      // The 20 trits, then 16 of them from byte o.
+      uint32_t d[5] = {e0.x, e0.y | (e1.x << 8), (e1.x >> 24) | (e1.y << 8) | (e2.x << 16),
+                       (e2.x >> 16) | (e2.y << 16) | (e3.x << 24), (e3.x >> 8) | (e3.y << 24)};
+      u4v y;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y[k] = o == 4 ? d[k + 1] : __builtin_amdgcn_alignbyte(d[k + 1], d[k], o);
+      if (c < chunks) __builtin_nontemporal_store(y, reinterpret_cast<u4v*>(trits) + c);
+    }
   }
+  count_errors(d_err, nbad);
 }
 
 // ---------------------------------------------------------------------------
@@ -266,13 +254,6 @@ __global__ void __launch_bounds__(kByteThreads) unpack_bytes_kernel(const uint8_
 // above 242, counted four bytes at a time; in the tail region odd bytes are
 // byte 25, whose pad digits 3 and 4 must be 1 (108 <= c <= 134).
 // ---------------------------------------------------------------------------
-
-// Bytes above 242 in a word: b >= 243 iff its top bit is set and its low
-// seven bits plus 13 reach 128 (no carry leaves a byte).
-__device__ inline int bad_main(uint32_t w) {
-  const uint32_t t = ((w & 0x7F7F7F7Fu) + 0x0D0D0D0Du) & w & 0x80808080u;
-  return __builtin_popcount(t);
-}
 
 // One byte at storage position pos.
 __device__ inline int bad_byte(uint32_t c, int64_t pos, int64_t main_bytes) {
@@ -612,8 +593,9 @@ hipError_t launch_pack(const int8_t* trits, int64_t n, uint8_t* codes, int32_t* 
 
 hipError_t launch_unpack(const uint8_t* codes, int64_t n, int8_t* trits, int32_t* d_err, hipStream_t s) {
   if ((reinterpret_cast<uintptr_t>(trits) & 15) == 0) {
-    const int64_t blocks = clamp_blocks((n + kPartGroups - 1) / kPartGroups, kPartMaxBlocks);
-    hipLaunchKernelGGL(unpack_kernel, dim3((unsigned)blocks), dim3(kPartThreads), 0, s, codes, n, trits, d_err);
+    const int64_t step = (int64_t)kUnpackThreads * kUnpackChunks * 16 / kGroup;   // groups
+    const int64_t blocks = clamp_blocks((n + step - 1) / step, kUnpackMaxBlocks);
+    hipLaunchKernelGGL(unpack_kernel, dim3((unsigned)blocks), dim3(kUnpackThreads), 0, s, codes, n, trits, d_err);
   } else {
     const int64_t blocks = clamp_blocks((kGroupBytes * n + kByteThreads - 1) / kByteThreads, kMaxBlocks);
     hipLaunchKernelGGL(unpack_bytes_kernel, dim3((unsigned)blocks), dim3(kByteThreads), 0, s, codes, n, trits,
