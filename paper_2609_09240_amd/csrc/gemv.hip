@@ -334,8 +334,8 @@ gemv_kernel(const uint16_t* __restrict__ x, int32_t G, int32_t ri, int32_t rows_
 // ------------------------------------------------------ a few batch rows
 // Y = X W^T for kB = 2..4 activation rows of one matrix: the GEMV above with
 // kB activation rows held in registers (33 each), so every code byte is
-// decoded once for all rows; for small batches this is cheaper than the
-// MFMA path (which must widen each code byte to 8 k-slots).  Records use the
+// decoded once for all rows, in the GEMV's order: a row of a batch has the
+// bits of tq_gemv, which the MFMA path's sums do not.  Records use the
 // host ranges and are taken by all threads after plane 0; X rows are staged
 // in LDS one after another.  Y is [kB][N].
 template <int kB>
@@ -822,7 +822,7 @@ hipError_t launch_gemv_batch(const MatDev& m, const uint16_t* X, int B, void* Y,
     }
   }
   // Staged rows of x that do not fit beside the table (down, K = 12288, at
-  // B = 4): the MFMA kernel takes the batch in one launch (16 us there,
+  // B = 4): the MFMA kernel takes the batch in one launch (12.6 us there,
   // against 20 us for two launches of two rows here).
   if (pi < 0) return hipErrorNotSupported;
   const int ri = T / SP;
