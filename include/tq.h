@@ -171,7 +171,9 @@ tq_status tq_unpack_fp16(const tq_matrix* m, uint16_t* w, void* stream);
  * s1*sum(t1*x_g) per two-plane group.  Accuracy:
  * |y - exact| <= 2e-3 * sum_g (|s0| + |mu0| + [two-plane](|mu| + |s1|)) *
  * ||x_g||_1 per output (|mu0| only with per-group offsets).  x and y must
- * not overlap the matrix buffers. */
+ * not overlap the matrix buffers.  Where x_g holds an infinity or NaN the
+ * sums above are taken as they stand: a trit of 0 under an infinity makes
+ * them, and the output, NaN. */
 tq_status tq_gemv(const tq_matrix* m, const uint16_t* x, void* y,
                   int32_t flags, void* stream);
 
@@ -191,7 +193,13 @@ tq_status tq_gemv_grouped(const tq_matrix* ms, int32_t n, const uint16_t* x,
  * work across batch sizes as the next step).
  *   X  fp16 [B][K] row-major; 16-byte aligned; 1 <= B <= TQ_MAX_BATCH
  *   Y  [B][N] row-major, fp16 or fp32 per flags; 4-byte aligned
- * Same accuracy bound as tq_gemv for every (b, r). */
+ * Same accuracy bound as tq_gemv for every (b, r).
+ * Inputs, scales and offsets that are not finite: the output is what the
+ * weights, formed one by one as tq_unpack_fp16 forms them (unrounded), give
+ * with X's row (an infinite input times a weight of 0 is NaN, times a weight
+ * that an offset makes nonzero +-inf), except in rows that take tq_gemv's
+ * sums (B = 1 and, where its launch fits, B = 2..4): there a trit of 0 under
+ * an infinite input gives NaN whatever the offsets are. */
 tq_status tq_gemm_smallbatch(const tq_matrix* m, const uint16_t* X, int32_t B,
                              void* Y, int32_t flags, void* stream);
 

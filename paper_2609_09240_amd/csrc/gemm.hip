@@ -85,6 +85,16 @@ struct TileArgs {
   int32_t rec_begin[kMaxRanges + 1];
 };
 
+// All arguments as a launch lays them out.
+struct KernelArgs {
+  const uint8_t* codes0;
+  const uint16_t* scale0;
+  const uint16_t* X;
+  const int32_t* rowptr1;
+  int32_t n_out, G, B, opts, nnz1;
+  TileArgs a;
+};
+
 // Dynamic LDS of a workgroup of R = 16 RT rows, NW waves and a chunk of C
 // groups (byte offsets): per wave 16 rows of a group of X, with 16 bytes
 // between rows so that one 16-byte read's 16 rows cover the banks; 64 zero
@@ -225,6 +235,73 @@ __device__ inline RecLoad load_record(const TileArgs& a, int nnz1, int k) {
   r.sm = (uint32_t)a.scale1[kk] | ((uint32_t)a.offset1[kk] << 16);
   r.gg = (int)a.gidx1[kk];
   return r;
+}
+
+__device__ inline bool not_finite(float a) { return (__builtin_bit_cast(uint32_t, a) & 0x7F800000u) == 0x7F800000u; }
+
+// An output whose sum is not finite, by the definition.  The sums of trits'
+// products say which outputs those are, but not what they are: an infinite
+// input under a zero trit puts 0 * inf into its group's sum, also where an
+// offset gives the weight a value, and a scale that is not finite meets the
+// group's sum and not each of its weights.  So the weights are formed one by
+// one, in tq_unpack_fp16's order, in the groups that hold a value that is not
+// finite (the others add a finite number, which changes nothing).  Finite inputs and scales never come here (no sum of theirs
+// leaves the range of fp32).
+template <bool kRec>
+__device__ __attribute__((always_inline)) inline float by_definition(
+    const __attribute__((address_space(4))) KernelArgs* p, int row, int b) {
+  const auto& a = p->a;
+  const int G = p->G, nnz1 = p->nnz1;
+  const uint8_t* codes0 = p->codes0;
+  const uint16_t* x = p->X + (int64_t)b * G * kGroup;
+  const bool has_off = a.offset0 != nullptr;
+  const uint32_t n0 = (uint32_t)p->n_out * (uint32_t)G;
+  int k = 0, ke = 0;
+  if constexpr (kRec) {   // in bounds whatever the row pointers hold
+    k = max(0, min(p->rowptr1[row], nnz1));
+    ke = max(0, min(p->rowptr1[row + 1], nnz1));
+  }
+  float sum = 0.f;
+  for (int g = 0; g < G && sum == sum; ++g, x += kGroup) {
+    const uint32_t f = (uint32_t)row * (uint32_t)G + (uint32_t)g;
+    const float s0 = h2f(p->scale0[(size_t)f]), mu0 = has_off ? h2f(a.offset0[(size_t)f]) : 0.f;
+    bool two = false;
+    float mu = 0.f, s1 = 0.f;
+    if constexpr (kRec) {
+      while (k < ke && (int)a.gidx1[k] < g) ++k;
+      two = k < ke && (int)a.gidx1[k] == g;
+      if (two) {
+        mu = h2f(a.offset1[k]);
+        s1 = h2f(a.scale1[k]);
+      }
+    }
+    bool look = not_finite(s0) || not_finite(mu0) || not_finite(mu) || not_finite(s1);
+    for (int i = 0; i < kGroup / 8; ++i) {
+      const u4v v = reinterpret_cast<const u4v*>(x)[i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) look |= (v[j] & 0x7C00u) == 0x7C00u || (v[j] & 0x7C000000u) == 0x7C000000u;
+    }
+    if (!look) continue;
+    for (int i = 0, c0 = 0, c1 = 0; i < kGroup; ++i) {
+      if (i % 5 == 0) {   // the next code byte; invalid codes read as zeros
+        const uint32_t j = (uint32_t)(i / 5);
+        c0 = codes0[j < 24u ? (size_t)(24u * f + j) : (size_t)(24u * n0 + 2u * f + (j - 24u))];
+        c0 = c0 > 242 ? 121 : c0;
+        if (two) {
+          const uint32_t kk = (uint32_t)k;
+          c1 = a.codes1[j < 24u ? (size_t)(24u * kk + j) : (size_t)(24u * (uint32_t)nnz1 + 2u * kk + (j - 24u))];
+          c1 = c1 > 242 ? 121 : c1;
+        }
+      }
+      float w = mu0 + mu;
+      w = w + s0 * (float)(c0 % 3 - 1);
+      if (two) w = w + s1 * (float)(c1 % 3 - 1);
+      sum = sum + w * h2f(x[i]);
+      c0 /= 3;
+      c1 /= 3;
+    }
+  }
+  return sum;
 }
 
 // RT, CT: row tiles of the workgroup, column tiles of the batch.  kRec: the
@@ -602,16 +679,33 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
 #pragma unroll
     for (int w = 1; w < NW; ++w) s += red[w * kItems + it];
     const int r = 16 * rt + (ln & 15), b = 16 * c + 4 * (ln >> 4);
+    auto store = [&](int i, float y) {
+      const int64_t o = (int64_t)(b + i) * n_out + row0 + r;
+      if (out_f32)
+        reinterpret_cast<float*>(a.Y)[o] = y;
+      else
+        reinterpret_cast<uint16_t*>(a.Y)[o] = (uint16_t)f2h(y);
+    };
     if (r < nrows) {
+      bool odd = false;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (b + i < B) {
-          const int64_t o = (int64_t)(b + i) * n_out + row0 + r;
-          if (out_f32)
-            reinterpret_cast<float*>(a.Y)[o] = s[i];
-          else
-            reinterpret_cast<uint16_t*>(a.Y)[o] = (uint16_t)f2h(s[i]);
+          store(i, s[i]);
+          odd |= not_finite(s[i]);
         }
+      if (odd) {
+        // The arguments where the launch put them, through a pointer the
+        // compiler knows nothing about (their loads are not done ahead of the
+        // branch, and nothing of them is held through the main loop).
+        auto args = (const __attribute__((address_space(4))) KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+#pragma unroll 1
+        for (int i = 0; i < min(4, B - b); ++i) {
+          const float y = by_definition<kRec>(args, row0 + r, b + i);
+          if (not_finite(y)) store(i, y);   // (a finite one is the sum of nothing: s[i] stands)
+        }
+      }
     }
   }
 }

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from gpu_helpers import Case, log
+from oracle import packed
 from paper_2609_09240_amd import synth, tq
 
 pytestmark = pytest.mark.gpu
@@ -69,3 +70,45 @@ def test_rows_that_are_not_finite(B, f2):
     t = inp.t0[:, 700]
     assert np.array_equal(got[1][one & (t == 1)], np.full((one & (t == 1)).sum(), np.inf, np.float32))
     assert np.array_equal(got[1][one & (t == -1)], np.full((one & (t == -1)).sum(), -np.inf, np.float32))
+
+
+def kinds(y):
+    """0 finite, 1 +inf, 2 -inf, 3 NaN."""
+    return np.select([np.isnan(y), np.isposinf(y), np.isneginf(y)], [3, 1, 2], 0)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("n_out,n_in,B,f2,offset0,mu,host", [
+    (300, 1024, 5, 0.3, True, None, True),
+    (300, 1024, 9, 0.3, False, None, False),
+    (300, 640, 20, 0.3, True, 0.0, True),     # records' offsets 0, as a matrix quantised with group offsets has
+    (4100, 256, 40, 0.1, False, None, True),  # two row tiles
+    (100, 512, 64, 0.0, True, None, True),
+    (100, 12800, 16, 0.1, True, None, True),  # two chunks of groups
+    (100, 512, 6, 0.0, False, None, True),    # one plane: 0 times infinity is NaN by the definition
+])
+def test_infinities_under_offsets(n_out, n_in, B, f2, offset0, mu, host, f32):
+    """An infinite input gives what the weights give one by one: +-inf also
+    where both trits are 0 and an offset is the weight, NaN where the weight is
+    0 or infinities cancel; and so do scales and offsets that are not finite."""
+    inp = synth.linear(n_out, n_in, f2, (47, n_out, n_in, B), offset0=offset0)
+    if mu is not None:
+        inp.mu1[:] = mu
+    inp.s0[7, 0], inp.s0[8, 1], inp.s0[9, 0] = np.inf, np.nan, 0.0
+    if offset0:
+        inp.mu0[10, 1], inp.mu0[11, 0] = -np.inf, 0.0
+    if inp.nnz1:
+        inp.s1[3], inp.s1[inp.nnz1 // 2] = -np.inf, np.nan
+    case = Case(inp, host_rowptr=host)
+    X = synth.activations(n_in, (47, n_out, n_in, 90), batch=B)
+    X[0, 100] = np.inf
+    X[1, n_in - 1] = -np.inf
+    X[2, 3], X[2, 200] = np.inf, np.inf
+    X[3, 127], X[3, n_in - 2] = np.inf, -np.inf
+    X[B - 1, 5], X[B - 1, 6] = np.inf, np.nan
+    got = tq.tq_gemm_smallbatch(case.gpu, torch.from_numpy(X).cuda(), out_f32=f32).cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        w = packed.dequantize(*case.oracle_args(), offset0=inp.mu0)
+        want = np.stack([(w * x.astype(np.float64)).sum(axis=1) for x in X])
+    np.testing.assert_array_equal(kinds(got), kinds(want))
+    assert (kinds(want)[0] == (3 if f2 == 0 and not offset0 else 1)).any()
