@@ -687,14 +687,11 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
         reinterpret_cast<uint16_t*>(a.Y)[o] = (uint16_t)f2h(y);
     };
     if (r < nrows) {
-      bool odd = false;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (b + i < B) {
-          store(i, s[i]);
-          odd |= not_finite(s[i]);
-        }
-      if (odd) {
+        if (b + i < B) store(i, s[i]);
+      // (one check for the four; a quad past B has nothing to do in the branch)
+      if (__builtin_expect(not_finite((s[0] + s[1]) + (s[2] + s[3])), 0)) {
         // The arguments where the launch put them, through a pointer the
         // compiler knows nothing about (their loads are not done ahead of the
         // branch, and nothing of them is held through the main loop).
