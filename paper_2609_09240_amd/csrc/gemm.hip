@@ -62,6 +62,7 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 
+constexpr int kCus = 256;
 constexpr int kLdsLimit = 160 * 1024;
 constexpr int kWaves = 8;                            // two per SIMD
 constexpr int kThreads = 64 * kWaves;
@@ -716,8 +717,31 @@ TileKernel tile_pick_rec(bool rec) {
 }
 
 // Most row tiles of a workgroup: the operands of a group's row tiles are kept
-// in registers for all column tiles.
-constexpr int most_row_tiles(int CT) { return CT > 1 ? 3 : 4; }
+// in registers for all column tiles.  Four with two column tiles take 256
+// registers, with three they spill (34.8 us at 16384 x 4096, B = 48, where
+// two rounds of two row tiles take 28.8).
+constexpr int most_row_tiles(int CT) { return CT > 2 ? 3 : 4; }
+
+// Row tiles: a workgroup fills a CU (table and staged data take its LDS), so
+// the time is the rounds of 256 workgroups times the time of one, which is
+// near 3 + row tiles in units of a tile (4096 inputs, B = 16: 7.8, 9.9, 11.7
+// and 16.5 us for 1 to 4 tiles in one round).  Over 1900 shapes of up to 40000
+// outputs the choice is within 0.1 % of the best of the four on average and 8 %
+// at most.  16384 x 4096, B = 17: 27.2 us with three tiles in two rounds, 20.7 with four in
+// one; 16400 x 4096, B = 16: 28.8 with four in two rounds, 21.9 with three.
+int row_tiles(int n_out, int CT) {
+  int best = 1;
+  int64_t cost = INT64_MAX;
+  for (int rt = 1; rt <= most_row_tiles(CT); ++rt) {
+    const int64_t wgs = ((int64_t)n_out + 16 * rt - 1) / (16 * rt);
+    const int64_t c = (wgs + kCus - 1) / kCus * (3 + rt);
+    if (c <= cost) {
+      cost = c;
+      best = rt;
+    }
+  }
+  return best;
+}
 
 template <int CT, int Q>
 TileKernel tile_pick(int RT, bool rec) {
@@ -744,9 +768,7 @@ hipError_t launch_gemm_smallbatch(const MatDev& m, const uint16_t* X, int B, voi
                                   hipStream_t s) {
   const int G = m.n_groups;
   const int CT = (B + 15) / 16;
-  // Rows per workgroup: about one workgroup per CU (256).
-  int RT = (m.n_out + 16 * 256 - 1) / (16 * 256);
-  RT = RT < most_row_tiles(CT) ? RT : most_row_tiles(CT);
+  const int RT = row_tiles(m.n_out, CT);
   const int R = 16 * RT;
   const int wgs = (m.n_out + R - 1) / R;
   // Chunks of equal size, as few as hold at most kMaxPairs pairs.

@@ -35,6 +35,10 @@ def sum_bound(case, X):
     (8200, 640, 64, 1.0, False, True),     # three row tiles, three passes everywhere
     (12300, 3200, 12, 1.0, True, False),   # four row tiles, 25 groups: two chunks, four passes
     (12300, 384, 48, 0.5, False, True),    # past three row tiles with several column tiles: several rounds
+    (12300, 384, 17, 0.5, False, True),    # four row tiles and two column tiles
+    (16384, 3200, 32, 0.3, True, False),   # the same, 25 groups in two chunks, every row tile full
+    (16400, 256, 16, 0.3, False, True),    # one row past a round of four row tiles: three
+    (16385, 128, 40, 1.0, False, True),    # and with three column tiles
 ])
 def test_tile_edges(n_out, n_in, B, f2, offset0, host):
     case = Case(synth.linear(n_out, n_in, f2, (41, n_out, n_in, B), offset0=offset0), host_rowptr=host)
