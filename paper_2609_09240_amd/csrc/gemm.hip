@@ -177,10 +177,14 @@ __device__ __attribute__((always_inline)) inline float4v mfma(u4v a, u4v b, floa
 }
 
 // Holds MFMA results back until they can be read anywhere.  The compiler puts
-// wait states between an MFMA and the first read of its result, but where a
-// branch lies between the two it can count those of the longer way round
-// only (seen on an `if` directly behind a chain: the first of the four sums
-// was read too early).
+// wait states between an MFMA and the first read of its result (8 for
+// v_mfma_f32_16x16x32_f16: `s_nop 7` in straight code), but where a branch lies
+// between the two it can count those of the longer way round only (seen on an
+// `if` directly behind a chain: the first of the four sums was read too early).
+// So it belongs between the last MFMA of a chain and every branch whose sides
+// read what the chain wrote, with all accumulators that may still be in
+// flight; where no branch lies between, nothing is needed.  Its 16 wait states
+// are twice this instruction's; one of 16 passes (32 x 32 tiles) wants more.
 __device__ __attribute__((always_inline)) inline void settle(float4v& a, float4v& b) {
   asm volatile("s_nop 15" : "+v"(a), "+v"(b));
 }
