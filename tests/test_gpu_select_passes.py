@@ -5,7 +5,9 @@ among ties that are not, and where every key left is taken."""
 
 import numpy as np
 import pytest
+import torch
 
+from paper_2609_09240_amd import tq
 from test_gpu_select import check
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +38,15 @@ def test_first_and_last(n_out, G, nnz):
     """One group, two groups, all groups."""
     n = n_out * G
     check(np.random.default_rng(3).exponential(1.0, n), n_out, G, n if nnz is None else nnz, f"{nnz} of {n}")
+
+
+@pytest.mark.parametrize("n_out,G", [(1, 1), (255, 1), (256, 1), (1, 256), (300, 17), (40000, 1), (33000, 128)])
+def test_nothing_to_select(n_out, G):
+    """No records: -1 for every group, zero row pointers, nothing behind them."""
+    n = n_out * G
+    e = torch.zeros(n, dtype=torch.float64, device="cuda")
+    rec = torch.full((n + 1,), 7, dtype=torch.int32, device="cuda")
+    rowptr = torch.full((n_out + 2,), 7, dtype=torch.int32, device="cuda")
+    tq.tq_select_two_plane(e, n_out, G, 0, rec_index=rec, rowptr1=rowptr)
+    assert (rec[:n] == -1).all() and rec[n].item() == 7
+    assert (rowptr[:n_out + 1] == 0).all() and rowptr[n_out + 1].item() == 7
