@@ -25,9 +25,12 @@
 // 3. Per tile: block-local scans give each selected group its record
 //    index, written to rec_index and gidx1, and the row pointers of the
 //    rows whose first group lies in the tile.
-// Up to kSmall groups one workgroup does all of it, with the keys in registers
-// (32768 groups: 35 us, 110 with the launches above, each some 2 us of launch
-// and 5 of atomics' round trips).
+// Up to kSmall groups one workgroup does all of it, with the keys in registers.
+// kSmall is what they hold: the one workgroup is the faster at every size it
+// takes (10 % of random energies, against the launches above, each some 2 us of
+// launch and 5 of atomics' round trips: 4000 groups 26 and 55 us, 8192 27 and
+// 58, 32768 34 and 60; with few distinct energies 39 and 61, 41 and 87, 53 and
+// 88), so the cost steps up where it ends (32800 groups: 57 us).
 // Counts are integers, so the result is deterministic and unique.
 
 #include <mutex>
