@@ -18,7 +18,9 @@ def sum_bound(case, X):
     """Each product is exact in fp32 and every term passes through at most
     K + 4 G roundings of 2^-24 (its group's sum, the scale, the other groups'
     and waves' sums), so the error is below that times sum |w x|, which the
-    acceptance bound holds 2e-3 times."""
+    acceptance bound holds 2e-3 times.  (At the longest rows that covers a
+    group: what is left out or taken twice there shows in
+    test_smallbatch_exact.py, whose sums are exact.)"""
     K = case.inp.n_in
     return case.bound(X) / 2e-3 * (K + 4 * (K // 128)) * 2.0 ** -24
 
