@@ -31,7 +31,7 @@ constexpr int kPartGroups = 64;     // groups per workgroup pass
 constexpr int kPartMaxBlocks = 2048;
 constexpr int kUnpackThreads = 256;   // one table entry each
 constexpr int kUnpackChunks = 4;
-constexpr int64_t kUnpackMaxBlocks = 1 << 14;
+constexpr int64_t kUnpackMaxBlocks = 1 << 14;   // (test_gpu_unpack_chunks.py goes past it: change both)
 
 constexpr int kByteThreads = 256;
 
