@@ -193,13 +193,20 @@ tq_status tq_gemv_grouped(const tq_matrix* ms, int32_t n, const uint16_t* x,
  * work across batch sizes as the next step).
  *   X  fp16 [B][K] row-major; 16-byte aligned; 1 <= B <= TQ_MAX_BATCH
  *   Y  [B][N] row-major, fp16 or fp32 per flags; 4-byte aligned
- * Same accuracy bound as tq_gemv for every (b, r).
- * Inputs, scales and offsets that are not finite: the output is what the
- * weights, formed one by one as tq_unpack_fp16 forms them (unrounded), give
- * with X's row (an infinite input times a weight of 0 is NaN, times a weight
- * that an offset makes nonzero +-inf), except in rows that take tq_gemv's
- * sums (B = 1 and, where its launch fits, B = 2..4): there a trit of 0 under
- * an infinite input gives NaN whatever the offsets are. */
+ * Same accuracy bound as tq_gemv for every (b, r).  A row's result depends on
+ * the row and on B, not on the other rows.
+ * B = 1 is tq_gemv.  B = 2..4 take tq_gemv's sums in its order, so that every
+ * row equals tq_gemv of that row (+0 and -0 aside), where the matrix has no
+ * records or carries rowptr1_host, B rows of x and the records' sums fit in
+ * LDS beside the decode table (B * K up to about 40000: K = 12288 at B = 3,
+ * not at B = 4) and the outputs fit in 767 workgroups (49000 at K = 4096 and
+ * B = 4, fewer at a larger K).  All other calls add on the matrix cores, in
+ * another order.
+ * Inputs, scales and offsets that are not finite: on the matrix cores the
+ * output is what the weights, formed one by one as tq_unpack_fp16 forms them
+ * (unrounded), give with X's row (an infinite input times a weight of 0 is
+ * NaN, times a weight that an offset makes nonzero +-inf); with tq_gemv's sums
+ * a trit of 0 under an infinite input gives NaN whatever the offsets are. */
 tq_status tq_gemm_smallbatch(const tq_matrix* m, const uint16_t* X, int32_t B,
                              void* Y, int32_t flags, void* stream);
 
@@ -334,8 +341,12 @@ tq_status tq_chain_plan(const tq_stage* stages, int32_t n_stages, tq_chain_info*
  * whenever it is reused for a plan with another stage count.  Layout: word
  * 0 counts completed calls, word 2 (int32 at byte 8) is a sticky error flag
  * that a call sets when one of its waits gave up (after about 0.1 s; the
- * outputs of that call are then unspecified), then one 64-byte slot per
- * workgroup. */
+ * outputs of that call are then unspecified).  The rest is the library's own:
+ * the running call's finished workgroups (word 1), its mode (word 16) and
+ * tickets (word 32), which every call finds and leaves 0, and behind byte 256
+ * one 64-byte slot per work item of a stage.  Nothing but the error flag may
+ * be written; a block whose call did not run to its end (a device reset, a
+ * copy taken meanwhile) goes through this function again. */
 tq_status tq_chain_sync_init(void* sync, const tq_chain_info* info, void* stream);
 
 /* Run every stage of a planned chain on `stream` (one launch).  `plan` is
