@@ -62,7 +62,7 @@ constexpr int kSpinLimit = 1 << 17;     // poll rounds (~0.1 s) before a wait gi
 constexpr int kDecideSpins = 64;        // poll rounds (~50 us) for all workgroups to start
 constexpr uint32_t kOpen = 0, kFixed = 1, kTickets = 2;
 constexpr int kSyncHeadBytes = 256;
-constexpr int kFlagStrideDw = 16;       // 64 bytes between workgroup flags
+constexpr int kFlagStrideDw = 16;       // 64 bytes between the items' flags
 static_assert(kXTailDw + 4 <= kXStrideDw - 2, "the last two dwords of an x slot are free");
 
 struct ChainSyncHead {

@@ -1,7 +1,8 @@
 """GPU parity of tq_gemm_smallbatch (B = 1: the GEMV; 2..4: the GEMV's decode
-per batch row; larger: the MFMA kernel over quads of groups, or the
-per-group fallback) against the fp64 oracle, per (batch row, output) within
-the same bound as the GEMV."""
+per batch row where its launch fits; otherwise the MFMA kernel, whose eight
+waves take a workgroup's groups in turn, in chunks of at most 1536 (row, group)
+pairs) against the fp64 oracle, per (batch row, output) within the same bound
+as the GEMV."""
 
 import numpy as np
 import pytest
@@ -74,13 +75,13 @@ def test_deterministic_mlp_shapes(name, B):
 
 @pytest.mark.parametrize("B", [3, 16, 40, 64])
 @pytest.mark.parametrize("n_out,n_in,f2", [
-    (5000, 512, 0.1),      # one quad of groups (seven of eight waves get none), two row tiles per workgroup
-    (13000, 256, 0.1),     # half a quad; four row tiles (three with four column tiles), ragged last workgroup
-    (16400, 256, 0.05),    # four row tiles with up to three column tiles
-    (300, 10240, 0.1),     # three quads per wave, the last waves' quads past the end of K
-    (40, 16384, 0.1),      # four quads per wave, the most the registers allow
-    (40, 16896, 0.1),      # more quads per wave than that: the per-group fallback kernel
-    (100, 8192, 1.0),      # every group two-plane: over 512 records per workgroup, staged in several batches
+    (5000, 512, 0.1),      # four groups (four of eight waves get none), two row tiles per workgroup
+    (13000, 256, 0.1),     # two groups; four row tiles (two, and two rounds, with three or more column tiles)
+    (16400, 256, 0.05),    # one row past a round of four row tiles: three, and two rounds of workgroups
+    (300, 10240, 0.1),     # one row tile, 80 groups in one chunk, ten a wave
+    (40, 16384, 0.1),      # 128 groups: two chunks of 64
+    (40, 16896, 0.1),      # 132 groups: two chunks of 66, which eight waves do not divide
+    (100, 8192, 1.0),      # every group two-plane: 1024 records per workgroup, staged in two sweeps
 ])
 def test_workgroup_layouts(B, n_out, n_in, f2):
     log(f"smallbatch layout B={B} {n_out}x{n_in} f2={f2}")
@@ -96,7 +97,7 @@ def test_workgroup_layouts(B, n_out, n_in, f2):
 @pytest.mark.parametrize("n_out,n_in,f2", [(5000, 512, 0.1), (300, 10240, 0.1), (100, 8192, 1.0)])
 def test_without_host_row_pointers(B, n_out, n_in, f2):
     """Without the host row pointers the MFMA kernel reads each workgroup's
-    record range from the device row pointers (after the codes): same
+    record range from the device row pointers: same
     results within the bound, for several column tiles and more than 512
     records per workgroup."""
     log(f"smallbatch device ranges B={B} {n_out}x{n_in} f2={f2}")
@@ -114,8 +115,8 @@ def test_without_host_row_pointers(B, n_out, n_in, f2):
     (100, 1024, 1.0),
 ])
 def test_group_offsets(B, n_out, n_in, f2):
-    """Per-group offsets on every group, through every workgroup layout and
-    the fallback kernel."""
+    """Per-group offsets on every group: one to three row tiles, one chunk and
+    two."""
     log(f"smallbatch offsets B={B} {n_out}x{n_in} f2={f2}")
     case = Case(synth.linear(n_out, n_in, f2, (19, n_out, n_in, B), offset0=True))
     X = synth.activations(n_in, (19, n_out, n_in, 97), batch=B, outlier_frac=0.01)
