@@ -244,69 +244,135 @@ __device__ inline RecLoad load_record(const TileArgs& a, int nnz1, int k) {
 
 __device__ inline bool not_finite(float a) { return (__builtin_bit_cast(uint32_t, a) & 0x7F800000u) == 0x7F800000u; }
 
-// An output whose sum is not finite, by the definition.  The sums of trits'
-// products say which outputs those are, but not what they are: an infinite
-// input under a zero trit puts 0 * inf into its group's sum, also where an
-// offset gives the weight a value, and a scale that is not finite meets the
-// group's sum and not each of its weights.  So the weights are formed one by
-// one, in tq_unpack_fp16's order, in the groups that hold a value that is not
-// finite (the others add a finite number, which changes nothing).  Finite inputs and scales never come here (no sum of theirs
-// leaves the range of fp32).
+// The arguments where the launch put them, through a pointer the compiler
+// knows nothing about: their loads are not done ahead of a rare branch, and
+// nothing of them is held through the main loop.
+typedef const __attribute__((address_space(4))) KernelArgs* ArgsPtr;
+__device__ __attribute__((always_inline)) inline ArgsPtr launch_args() {
+  ArgsPtr p = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// What a quarter of group g of a row (code bytes 7 quarter ..) adds to the
+// row's output, weight by weight in tq_unpack_fp16's order.  k0, k1: the row's
+// records; x: the inputs of the batch row.
 template <bool kRec>
-__device__ __attribute__((always_inline)) inline float by_definition(
-    const __attribute__((address_space(4))) KernelArgs* p, int row, int b) {
-  const auto& a = p->a;
-  const int G = p->G, nnz1 = p->nnz1;
-  const uint8_t* codes0 = p->codes0;
-  const uint16_t* x = p->X + (int64_t)b * G * kGroup;
-  const bool has_off = a.offset0 != nullptr;
-  const uint32_t n0 = (uint32_t)p->n_out * (uint32_t)G;
-  int k = 0, ke = 0;
-  if constexpr (kRec) {   // in bounds whatever the row pointers hold
-    k = max(0, min(p->rowptr1[row], nnz1));
-    ke = max(0, min(p->rowptr1[row + 1], nnz1));
+__device__ __attribute__((always_inline)) inline float quarter_sum(ArgsPtr p, int row, int g, int quarter, int k0, int k1,
+                                                                   const uint16_t* x) {
+  const uint32_t n0 = (uint32_t)p->n_out * (uint32_t)p->G, n1 = (uint32_t)p->nnz1;
+  const uint32_t f = (uint32_t)row * (uint32_t)p->G + (uint32_t)g;
+  const float s0 = h2f(p->scale0[(size_t)f]);
+  float mu = p->a.offset0 != nullptr ? h2f(p->a.offset0[(size_t)f]) : 0.f, s1 = 0.f;
+  bool two = false;
+  if constexpr (kRec) {
+    const int end = k1;
+    while (k0 < k1) {   // the first record at or behind g
+      const int mid = (k0 + k1) >> 1;
+      if ((int)p->a.gidx1[mid] < g) k0 = mid + 1;
+      else k1 = mid;
+    }
+    two = k0 < end && (int)p->a.gidx1[k0] == g;
+    if (two) {
+      mu = mu + h2f(p->a.offset1[k0]);
+      s1 = h2f(p->a.scale1[k0]);
+    }
   }
   float sum = 0.f;
-  for (int g = 0; g < G && sum == sum; ++g, x += kGroup) {
-    const uint32_t f = (uint32_t)row * (uint32_t)G + (uint32_t)g;
-    const float s0 = h2f(p->scale0[(size_t)f]), mu0 = has_off ? h2f(a.offset0[(size_t)f]) : 0.f;
-    bool two = false;
-    float mu = 0.f, s1 = 0.f;
+  for (uint32_t j = 7u * (uint32_t)quarter; j < min(7u * (uint32_t)quarter + 7u, (uint32_t)kGroupBytes); ++j) {
+    int c0 = p->codes0[j < 24u ? (size_t)(24u * f + j) : (size_t)(24u * n0 + 2u * f + (j - 24u))], c1 = 121;
     if constexpr (kRec) {
-      while (k < ke && (int)a.gidx1[k] < g) ++k;
-      two = k < ke && (int)a.gidx1[k] == g;
-      if (two) {
-        mu = h2f(a.offset1[k]);
-        s1 = h2f(a.scale1[k]);
-      }
+      const uint32_t k = (uint32_t)k0;
+      if (two) c1 = p->a.codes1[j < 24u ? (size_t)(24u * k + j) : (size_t)(24u * n1 + 2u * k + (j - 24u))];
     }
-    bool look = not_finite(s0) || not_finite(mu0) || not_finite(mu) || not_finite(s1);
-    for (int i = 0; i < kGroup / 8; ++i) {
-      const u4v v = reinterpret_cast<const u4v*>(x)[i];
+    c0 = c0 > 242 ? 121 : c0;   // (invalid codes read as zeros)
+    c1 = c1 > 242 ? 121 : c1;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) look |= (v[j] & 0x7C00u) == 0x7C00u || (v[j] & 0x7C000000u) == 0x7C000000u;
-    }
-    if (!look) continue;
-    for (int i = 0, c0 = 0, c1 = 0; i < kGroup; ++i) {
-      if (i % 5 == 0) {   // the next code byte; invalid codes read as zeros
-        const uint32_t j = (uint32_t)(i / 5);
-        c0 = codes0[j < 24u ? (size_t)(24u * f + j) : (size_t)(24u * n0 + 2u * f + (j - 24u))];
-        c0 = c0 > 242 ? 121 : c0;
-        if (two) {
-          const uint32_t kk = (uint32_t)k;
-          c1 = a.codes1[j < 24u ? (size_t)(24u * kk + j) : (size_t)(24u * (uint32_t)nnz1 + 2u * kk + (j - 24u))];
-          c1 = c1 > 242 ? 121 : c1;
-        }
-      }
-      float w = mu0 + mu;
-      w = w + s0 * (float)(c0 % 3 - 1);
+    for (int i = 0; i < 5; ++i) {
+      const int at = 5 * (int)j + i;
+      float w = mu + s0 * (float)(c0 % 3 - 1);
       if (two) w = w + s1 * (float)(c1 % 3 - 1);
-      sum = sum + w * h2f(x[i]);
+      if (at < kGroup) sum = sum + w * h2f(x[kGroup * g + at]);
       c0 /= 3;
       c1 /= 3;
     }
   }
   return sum;
+}
+
+// Outputs of a wave's 16 x 16 tile whose sums are not finite, by the
+// definition.  The sums of trits' products say which outputs those are, but
+// not what they are: an infinite input under a zero trit puts 0 * inf into its
+// group's sum, also where an offset gives the weight a value, and a scale that
+// is not finite meets the group's sum and not each of its weights.  So the
+// weights are formed one by one, in the groups where the batch row holds a
+// value that is not finite (the others add a finite number, which changes
+// nothing; with a scale or offset that is not finite in the tile's rows, in
+// every group).  Lanes n, n + 16, n + 32 and n + 48 share weight row n.  Finite
+// inputs and scales never come here (no sum of theirs leaves the range of
+// fp32).  One infinity in a row of X: 12288 x 4096, B = 16, 14.3 -> 25.6 us;
+// one in each of 64 rows of X, 27 -> 291 (a lane that reads its output's whole
+// row alone takes 269 and 675).  The check costs a call 0.09 us, 0.6 % over 960
+// shapes of one round.  row0, nrows: the tile's weight rows; b0: its first batch row;
+// s: the lane's four sums; store(b, y): an output of the lane's weight row.
+template <bool kRec, typename Store>
+__device__ __attribute__((always_inline)) inline void redo_tile(int row0, int nrows, int b0, float4v s, const Store& store) {
+  const ArgsPtr p = launch_args();
+  const int G = p->G, lane = (int)__lane_id(), n = lane & 15, q = lane >> 4;
+  const int row = row0 + min(n, nrows - 1);
+  int k0 = 0, k1 = 0, every = -1;   // (every: not known yet)
+  if constexpr (kRec) {   // in bounds whatever the row pointers hold
+    k0 = max(0, min(p->rowptr1[row], p->nnz1));
+    k1 = max(0, min(p->rowptr1[row + 1], p->nnz1));
+  }
+#pragma unroll 1
+  for (int j = 0; j < min(16, p->B - b0); ++j) {
+    const float y = (j & 2) ? ((j & 1) ? s[3] : s[2]) : ((j & 1) ? s[1] : s[0]);
+    if (__ballot(q == j >> 2 && n < nrows && not_finite(y)) == 0) continue;
+    if (every < 0) {
+      bool bad = false;
+#pragma unroll 4
+      for (int g = q; g < G; g += 4) {
+        const size_t f = (size_t)((uint32_t)row * (uint32_t)G + (uint32_t)g);
+        bad |= not_finite(h2f(p->scale0[f]));
+        if (p->a.offset0 != nullptr) bad |= not_finite(h2f(p->a.offset0[f]));
+      }
+      if constexpr (kRec) {
+#pragma unroll 4
+        for (int k = k0 + q; k < k1; k += 4) bad |= not_finite(h2f(p->a.offset1[k])) || not_finite(h2f(p->a.scale1[k]));
+      }
+      every = __ballot(bad) != 0;
+    }
+    const uint16_t* x = p->X + (int64_t)(b0 + j) * G * kGroup;
+    float sum = 0.f;
+    bool known = false;   // every row's output is NaN
+#pragma unroll 1
+    for (int g0 = 0; g0 < G && !known; g0 += 16) {   // lanes 16 i .. hold the inputs of groups g0 + 4 t + i
+      u4v v[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        v[t] = *reinterpret_cast<const u4v*>(x + kGroup * min(g0 + 4 * t + q, G - 1) + 8 * n);
+#pragma unroll 1
+      for (int t = 0; t < 4 && !known; ++t) {
+        const u4v u = t == 0 ? v[0] : (t == 1 ? v[1] : (t == 2 ? v[2] : v[3]));
+        bool bad = every != 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bad |= (u[i] & 0x7C00u) == 0x7C00u || (u[i] & 0x7C000000u) == 0x7C000000u;
+        const uint64_t m = __ballot(bad);
+#pragma unroll 1
+        for (int i = 0; i < 4 && !known; ++i) {
+          const int g = g0 + 4 * t + i;
+          if (g >= G || ((m >> (16 * i)) & 0xFFFFu) == 0) continue;
+          sum += quarter_sum<kRec>(p, row, g, q, k0, k1, x);
+          sum += __shfl_xor(sum, 16);   // the row's other quarters; the sums of groups are kept in quarter 0
+          sum += __shfl_xor(sum, 32);
+          known = __ballot(sum == sum) == 0;
+          sum = q == 0 || not_finite(sum) ? sum : 0.f;
+        }
+      }
+    }
+    if (q == j >> 2 && n < nrows && not_finite(sum)) store(b0 + j, sum);
+  }
 }
 
 // RT, CT: row tiles of the workgroup, column tiles of the batch.  kRec: the
@@ -684,8 +750,8 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
 #pragma unroll
     for (int w = 1; w < NW; ++w) s += red[w * kItems + it];
     const int r = 16 * rt + (ln & 15), b = 16 * c + 4 * (ln >> 4);
-    auto store = [&](int i, float y) {
-      const int64_t o = (int64_t)(b + i) * n_out + row0 + r;
+    auto store = [&](int bb, float y) {
+      const int64_t o = (int64_t)bb * n_out + row0 + r;
       if (out_f32)
         reinterpret_cast<float*>(a.Y)[o] = y;
       else
@@ -694,21 +760,13 @@ tile_kernel(const uint8_t* __restrict__ codes0, const uint16_t* __restrict__ sca
     if (r < nrows) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (b + i < B) store(i, s[i]);
-      // (one check for the four; a quad past B has nothing to do in the branch)
-      if (__builtin_expect(not_finite((s[0] + s[1]) + (s[2] + s[3])), 0)) {
-        // The arguments where the launch put them, through a pointer the
-        // compiler knows nothing about (their loads are not done ahead of the
-        // branch, and nothing of them is held through the main loop).
-        auto args = (const __attribute__((address_space(4))) KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(args));
-#pragma unroll 1
-        for (int i = 0; i < min(4, B - b); ++i) {
-          const float y = by_definition<kRec>(args, row0 + r, b + i);
-          if (not_finite(y)) store(i, y);   // (a finite one is the sum of nothing: s[i] stands)
-        }
-      }
+        if (b + i < B) store(b + i, s[i]);
     }
+    // (One check for a lane's four sums, outputs or not; the quads of X that
+    // were not loaded may hold anything.)
+    bool odd = not_finite((s[0] + s[1]) + (s[2] + s[3]));
+    if constexpr (kQuads < 4) odd = odd && (ln >> 4) < kQuads;
+    if (__builtin_expect(__ballot(odd) != 0, 0)) redo_tile<kRec>(row0 + 16 * rt, nrows - 16 * rt, 16 * c, s, store);
   }
 }
 
