@@ -45,8 +45,8 @@
 // waves a SIMD), and below 8 us the set-up of a launch.  Graph-timed, weights
 // from HBM, 10 % two-plane groups, before (quads of groups, s0 and s1 put into
 // fp16 weights, plane 1 under a per-lane branch) and now:
-//   12288 x 4096  B = 16 15.8 -> 12.1 us, B = 32 20.7 -> 16.3, B = 64 28.0 -> 25.5
-//   4096 x 12288  B = 4 14.8 -> 13.3, B = 16 18.9 -> 14.8, B = 64 54.0 -> 35.5
+//   12288 x 4096  B = 16 15.8 -> 12.3 us, B = 32 20.7 -> 16.6, B = 64 28.0 -> 26.1
+//   4096 x 12288  B = 4 14.8 -> 12.9, B = 16 18.9 -> 14.6, B = 64 54.0 -> 34.9
 //   4096 x 4096   B = 16 8.7 -> 7.8, B = 64 22.9 -> 13.3
 //   4096 x 20480  B = 16 928 -> 20.7 (a kernel of its own for a long K before)
 // A ring of 4 to 12 groups is slower (13.1 us at 12288 x 4096, B = 16): the

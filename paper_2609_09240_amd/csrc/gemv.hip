@@ -825,7 +825,7 @@ hipError_t launch_gemv_batch(const MatDev& m, const uint16_t* X, int B, void* Y,
     }
   }
   // Staged rows of x that do not fit beside the table (down, K = 12288, at
-  // B = 4): the MFMA kernel takes the batch in one launch (13.3 us there,
+  // B = 4): the MFMA kernel takes the batch in one launch (13 us there,
   // against 20 us for two launches of two rows here).
   if (pi < 0) return hipErrorNotSupported;
   const int ri = T / SP;
