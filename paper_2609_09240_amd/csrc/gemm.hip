@@ -786,8 +786,8 @@ constexpr int most_row_tiles(int CT) { return CT > 2 ? 3 : 4; }
 
 // Row tiles: a workgroup fills a CU (table and staged data take its LDS), so
 // the time is the rounds of 256 workgroups times the time of one, which is
-// near 3 + row tiles in units of a tile (4096 inputs, B = 16: 7.8, 9.9, 11.7
-// and 16.5 us for 1 to 4 tiles in one round).  Over 1900 shapes of up to 40000
+// near 3 + row tiles in units of a tile (4096 inputs, B = 16: 7.9, 9.9, 11.7
+// and 16.5 us for 1 to 4 tiles in one round; the last stages two chunks).  Over 3500 shapes of up to 40000
 // outputs the choice is within 0.1 % of the best of the four on average and 8 %
 // at most.  16384 x 4096, B = 17: 27.2 us with three tiles in two rounds, 20.7 with four in
 // one; 16400 x 4096, B = 16: 28.8 with four in two rounds, 21.9 with three.
