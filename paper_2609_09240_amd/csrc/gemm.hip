@@ -312,8 +312,8 @@ __device__ __attribute__((always_inline)) inline float quarter_sum(ArgsPtr p, in
 // inputs and scales never come here (no sum of theirs leaves the range of
 // fp32).  One infinity in a row of X: 12288 x 4096, B = 16, 14.3 -> 25.6 us;
 // one in each of 64 rows of X, 27 -> 291 (a lane that reads its output's whole
-// row alone takes 269 and 675).  The check costs a call 0.09 us, 0.6 % over 960
-// shapes of one round.  row0, nrows: the tile's weight rows; b0: its first batch row;
+// row alone takes 269 and 675).  The check costs a call 0.09 us, 0.6 % over
+// 960 shapes.  row0, nrows: the tile's weight rows; b0: its first batch row;
 // s: the lane's four sums; store(b, y): an output of the lane's weight row.
 template <bool kRec, typename Store>
 __device__ __attribute__((always_inline)) inline void redo_tile(int row0, int nrows, int b0, float4v s, const Store& store) {
@@ -787,10 +787,11 @@ constexpr int most_row_tiles(int CT) { return CT > 2 ? 3 : 4; }
 // Row tiles: a workgroup fills a CU (table and staged data take its LDS), so
 // the time is the rounds of 256 workgroups times the time of one, which is
 // near 3 + row tiles in units of a tile (4096 inputs, B = 16: 7.9, 9.9, 11.7
-// and 16.5 us for 1 to 4 tiles in one round; the last stages two chunks).  Over 3500 shapes of up to 40000
-// outputs the choice is within 0.1 % of the best of the four on average and 8 %
-// at most.  16384 x 4096, B = 17: 27.2 us with three tiles in two rounds, 20.7 with four in
-// one; 16400 x 4096, B = 16: 28.8 with four in two rounds, 21.9 with three.
+// and 16.5 us for 1 to 4 tiles in one round; the last stages two chunks).
+// Over 3500 shapes of up to 40000 outputs the choice is within 0.1 % of the
+// best of the four on average and 8 % at most.  16384 x 4096, B = 17: 27.2 us
+// with three tiles in two rounds, 20.7 with four in one; 16400 x 4096, B = 16:
+// 28.8 with four in two rounds, 21.9 with three.
 int row_tiles(int n_out, int CT) {
   int best = 1;
   int64_t cost = INT64_MAX;
